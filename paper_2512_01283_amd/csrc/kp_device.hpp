@@ -26,6 +26,8 @@ __device__ __forceinline__ float k_cos(float x) { return cosf(x); }
 __device__ __forceinline__ double k_cos(double x) { return cos(x); }
 __device__ __forceinline__ void k_sincospi(float x, float* s, float* c) { sincospif(x, s, c); }
 __device__ __forceinline__ void k_sincospi(double x, double* s, double* c) { sincospi(x, s, c); }
+__device__ __forceinline__ float k_fma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double k_fma(double a, double b, double c) { return fma(a, b, c); }
 template <typename R> __device__ __forceinline__ R k_inf();
 template <> __device__ __forceinline__ float k_inf<float>() { return __builtin_huge_valf(); }
 template <> __device__ __forceinline__ double k_inf<double>() { return __builtin_huge_val(); }
@@ -44,8 +46,8 @@ __device__ __forceinline__ void philox4x64_10(uint64_t x0, uint64_t x1, uint64_t
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t a = 0xD2E7470EE14C6C93ull, b = 0xCA5A826395121157ull;
-    uint64_t hi0 = __umul64hi(a, x0), lo0 = a * x0;
-    uint64_t hi1 = __umul64hi(b, x2), lo1 = b * x2;
+    const unsigned __int128 p0 = (unsigned __int128)a * x0, p1 = (unsigned __int128)b * x2;
+    const uint64_t hi0 = (uint64_t)(p0 >> 64), lo0 = (uint64_t)p0, hi1 = (uint64_t)(p1 >> 64), lo1 = (uint64_t)p1;
     uint64_t y0 = hi1 ^ x1 ^ k0, y2 = hi0 ^ x3 ^ k1;
     x0 = y0; x1 = lo1; x2 = y2; x3 = lo0;
     k0 += 0x9E3779B97F4A7C15ull;
@@ -74,10 +76,12 @@ __device__ __forceinline__ V3<R> cross(const V3<R>& a, const V3<R>& b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
 
-// azimuth cosine/sine of a direction, phi = 0 at the pole
+// azimuth cosine/sine of a direction, phi = 0 at the pole (the sum's one
+// rounding of a product written out: which of the two squares the compiler
+// fuses otherwise depends on the code around the call)
 template <typename R>
 __device__ __forceinline__ void azimuth(const V3<R>& n, R& cp, R& sp, R& st) {
-  R r2 = n.x * n.x + n.y * n.y;
+  R r2 = k_fma(n.y, n.y, n.x * n.x);
   st = k_sqrt(r2);
   if (r2 <= (R)KP_POLE2) { cp = (R)1; sp = (R)0; }
   else { R inv = (R)1 / st; cp = n.x * inv; sp = n.y * inv; }

@@ -74,35 +74,70 @@ struct Packet {
   R I, Q, U, V;       // Stokes vector in the lab basis of n
   R w0;               // initial weight
   R tau_path;         // sum of |continuous extinction exponent| along the path
-  R u0, u1, u2, u3;   // uniforms of the Philox block `blk`
-  double e_abs, e_scat, e_gain;
+  double e_abs;
   double ks, ke;      // per-wavelength kappa_sca and kappa_ext times the cell size, held
   R ka;               // in registers (no dependent load per step); ka = kappa_abs dx
   float rho;          // density of the current cell when the grid holds it (loaded on
                       // entering the cell, one step before its use)
-  uint64_t pid, hash;
-  int64_t last;
+  uint32_t last;      // cell of the last step (~0: none)
   int ci, cj, ck;
   int leaf, lvl;      // composite mesh: the leaf block (ci..ck local to it) and its level
-  uint32_t draw, blk;
-  int events, steps, trials, lam, rr;
+  int events, steps, lam;
 };
 
-template <typename R>
-__device__ __forceinline__ R next_uniform(Packet<R>& p, uint64_t seed) {
-  uint32_t d = p.draw++;
-  uint32_t b = d >> 2;
-  if (b != p.blk) {
+// The part of a packet's state that only scattering, roulette and its start
+// and end touch, in LDS (one lane per column, so a wavefront's access to one
+// field is conflict-free): kept in registers it costs the step's kernels a
+// wave per SIMD.
+struct Cold {
+  uint64_t pid[64], hash[64];
+  double e_scat[64], e_gain[64];
+  float u[8][64];     // uniforms of the last two Philox blocks: draw d at u[d & 7]
+                      // (23 bits and a half: exact in FP32)
+  uint32_t draw[64];  // uniforms consumed
+  uint32_t blk[64];   // the newest block in u (~0: none)
+  uint32_t trials[64], rr[64];
+};
+struct ColdRef {
+  Cold& c;
+  int l;
+  __device__ __forceinline__ uint64_t& pid() const { return c.pid[l]; }
+  __device__ __forceinline__ uint64_t& hash() const { return c.hash[l]; }
+  __device__ __forceinline__ double& e_scat() const { return c.e_scat[l]; }
+  __device__ __forceinline__ double& e_gain() const { return c.e_gain[l]; }
+  __device__ __forceinline__ uint32_t& draw() const { return c.draw[l]; }
+  __device__ __forceinline__ uint32_t& blk() const { return c.blk[l]; }
+  __device__ __forceinline__ uint32_t& trials() const { return c.trials[l]; }
+  __device__ __forceinline__ uint32_t& rr() const { return c.rr[l]; }
+  __device__ __forceinline__ float& u(uint32_t d) const { return c.u[d & 7u][l]; }
+};
+
+// block b of the packet's stream, unless it is the newest one already
+__device__ __forceinline__ void need_block(const ColdRef& k, uint32_t b, uint64_t seed, int lam) {
+  if (b != k.blk()) {
     uint64_t w[4];
-    philox4x64_10(p.pid, (uint64_t)b, 0ull, 0ull, seed, (uint64_t)p.lam, w);
-    p.u0 = word_uniform<R>(w[0]);
-    p.u1 = word_uniform<R>(w[1]);
-    p.u2 = word_uniform<R>(w[2]);
-    p.u3 = word_uniform<R>(w[3]);
-    p.blk = b;
+    philox4x64_10(k.pid(), (uint64_t)b, 0ull, 0ull, seed, (uint64_t)lam, w);
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) k.u(4 * b + i) = word_uniform<float>(w[i]);
+    k.blk() = b;
   }
-  uint32_t k = d & 3u;
-  return k == 0 ? p.u0 : (k == 1 ? p.u1 : (k == 2 ? p.u2 : p.u3));
+}
+
+__device__ __forceinline__ float next_uniform(const ColdRef& k, uint64_t seed, int lam) {
+  const uint32_t d = k.draw();
+  k.draw() = d + 1;
+  need_block(k, d >> 2, seed, lam);
+  return k.u(d);
+}
+
+// The next four uniforms, draws d .. d + 3, in one visit of the generator
+// (they lie in at most two blocks, of which the older is in u already); the
+// caller consumes three or four of them, so that the blocks held always
+// cover the next draw.
+__device__ __forceinline__ void next_four(const ColdRef& k, uint32_t d, uint64_t seed, int lam, float u[4]) {
+  need_block(k, (d + 3) >> 2, seed, lam);
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) u[i] = k.u(d + i);
 }
 
 // Dimensionless extinction coefficients for a direction with cos(theta') =
@@ -274,30 +309,44 @@ __device__ __forceinline__ uint64_t cell_index(const Packet<R>& p, const Transpo
 }
 
 template <typename R, bool ALIGNED, bool SPHERE, bool MESH>
-__device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
+__device__ bool init_packet(Packet<R>& p, const ColdRef& k, uint64_t g, const TransportArgs& a) {
   int lo = 0, hi = a.n_lambda - 1;
   while (lo < hi) {  // last wavelength whose first index <= g
     int mid = (lo + hi + 1) >> 1;
     if (a.dust[mid].first <= g) lo = mid; else hi = mid - 1;
   }
   p.lam = lo;
-  p.pid = g - a.dust[lo].first;
-  p.draw = 0;
-  p.blk = 0xffffffffu;
+  k.pid() = g - a.dust[lo].first;
+  k.blk() = 0xffffffffu;
   p.w0 = (R)a.dust[lo].w0;
   p.ks = a.dust[lo].ks_cell;
   p.ke = a.dust[lo].ke_cell;
   p.ka = (R)a.dust[lo].ka_cell;
-  p.e_abs = 0.0; p.e_scat = 0.0; p.e_gain = 0.0;
+  p.e_abs = 0.0;
+  k.e_scat() = 0.0;
+  k.e_gain() = 0.0;
   p.tau_path = (R)0;
-  p.events = 0; p.steps = 0; p.trials = 0; p.rr = 0;
-  p.hash = 14695981039346656037ull;
-  p.last = -1;
+  p.events = 0; p.steps = 0;
+  k.trials() = 0;
+  k.rr() = 0;
+  k.hash() = 14695981039346656037ull;
+  p.last = 0xffffffffu;
+  // the draws of the start: for thermal emission the cell and three
+  // coordinates first, then two for the direction and one for the depth
+  float ue[4] = {0.f, 0.f, 0.f, 0.f}, us[4];
+  uint32_t d0 = 0;
+  if (a.src_kind == 2) {
+    next_four(k, 0, a.seed, lo, ue);
+    d0 = 4;
+  }
+  next_four(k, d0, a.seed, lo, us);
+  k.draw() = d0 + 3;
+  const double u0 = (double)us[0], u1 = (double)us[1];
   bool in = true;
   if (a.src_kind == 2) {
     const uint64_t c = emission_cell(a.em_cdf + (uint64_t)lo * a.ncell,
                                      a.em_guide + (uint64_t)lo * (a.ncell + 1), a.ncell,
-                                     (double)next_uniform(p, a.seed));
+                                     (double)ue[0]);
     if (MESH) {
       // cell c of the mesh: leaf c / block^3, local cell x fastest; the
       // cell-length constants of the leaf's level
@@ -316,10 +365,9 @@ __device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
       p.cj = (int)((c / (uint64_t)a.nx) % (uint64_t)a.ny);
       p.ck = (int)(c / ((uint64_t)a.nx * (uint64_t)a.ny));
     }
-    p.fx = (double)next_uniform(p, a.seed);
-    p.fy = (double)next_uniform(p, a.seed);
-    p.fz = (double)next_uniform(p, a.seed);
-    const double u0 = (double)next_uniform(p, a.seed), u1 = (double)next_uniform(p, a.seed);
+    p.fx = (double)ue[1];
+    p.fy = (double)ue[2];
+    p.fz = (double)ue[3];
     isotropic_dir(p, u0, u1);
     const double w = a.dust[lo].w0;
     if (SPHERE) {
@@ -339,7 +387,6 @@ __device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
     }
     p.rho = a.rho[c];
   } else {
-    const double u0 = (double)next_uniform(p, a.seed), u1 = (double)next_uniform(p, a.seed);
     if (a.src_kind == 1) {
       p.nx = a.dx_; p.ny = a.dy_; p.nz = a.dz_;
     } else {
@@ -362,7 +409,7 @@ __device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
       if (in) mesh_place(p, a, t, X);
       p.rho = in ? a.rho[cell_index<true>(p, a)] : 0.f;
       p.rnx = 1.0 / p.nx; p.rny = 1.0 / p.ny; p.rnz = 1.0 / p.nz;
-      p.tau = -log((double)next_uniform(p, a.seed));
+      p.tau = -log((double)us[2]);
       return in;
     }
     int ci[3];
@@ -387,7 +434,7 @@ __device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
     p.rho = in ? a.rho[(uint64_t)p.ci + (uint64_t)a.nx * ((uint64_t)p.cj + (uint64_t)a.ny * p.ck)] : 0.f;
   }
   p.rnx = 1.0 / p.nx; p.rny = 1.0 / p.ny; p.rnz = 1.0 / p.nz;
-  p.tau = -log((double)next_uniform(p, a.seed));
+  p.tau = -log((double)us[2]);
   return in;
 }
 
@@ -400,11 +447,15 @@ __device__ bool init_packet(Packet<R>& p, uint64_t g, const TransportArgs& a) {
 // product of two basis components is written with cos^2 p, sin^2 p,
 // cos p sin p (from n by one reciprocal of nx^2 + ny^2) and sin t cos p = nx,
 // sin t sin p = ny: no square root per step.  At the pole (phi = 0) cos p = 1
-// and sin t = sqrt(nx^2 + ny^2).
+// and sin t = sqrt(nx^2 + ny^2).  Jp, Jm: J_I + J_Q and J_I - J_Q.  Every sum of
+// two products is written as one product and one fused multiply-add, so that
+// a kernel's FP32 results do not depend on which of the two the compiler fuses
+// in the code around it.
 template <typename R, int NC>
-__device__ __forceinline__ void coherency(const V3<R>& n, R JI, R JQ, R JU, R JV, R w,
+__device__ __forceinline__ void coherency(const V3<R>& n, R Jp, R Jm, R JU, R JV, R w,
                                           R out[NC]) {
-  const R r2 = n.x * n.x + n.y * n.y;
+#pragma clang fp contract(off)
+  const R r2 = k_fma(n.y, n.y, n.x * n.x);
   R px, py, cc, ss, cs;  // sin t cos p, sin t sin p, cos^2 p, sin^2 p, cos p sin p
   if (r2 <= (R)KP_POLE2) {
     px = k_sqrt(r2); py = (R)0; cc = (R)1; ss = (R)0; cs = (R)0;
@@ -412,15 +463,15 @@ __device__ __forceinline__ void coherency(const V3<R>& n, R JI, R JQ, R JU, R JV
     const R ir = (R)1 / r2;
     px = n.x; py = n.y; cc = n.x * n.x * ir; ss = n.y * n.y * ir; cs = n.x * n.y * ir;
   }
-  R a = (R)0.5 * (JI + JQ) * w, b = (R)0.5 * (JI - JQ) * w, u = (R)0.5 * JU * w;
-  R v = (R)-0.5 * JV * w;
-  const R an2 = a * n.z * n.z, un = u * n.z;
-  out[0] = an2 * cc + b * ss - (R)2 * un * cs;
-  out[1] = an2 * ss + b * cc + (R)2 * un * cs;
+  const R a = (R)0.5 * Jp * w, b = (R)0.5 * Jm * w, u = (R)0.5 * JU * w;
+  const R v = (R)-0.5 * JV * w;
+  const R an = a * n.z, an2 = an * n.z, un = u * n.z, un2 = un + un;
+  out[0] = k_fma(-un2, cs, k_fma(b, ss, an2 * cc));
+  out[1] = k_fma(un2, cs, k_fma(an2, ss, b * cc));
   out[2] = a * r2;
-  out[3] = (an2 - b) * cs + un * (cc - ss);
-  out[4] = -a * n.z * px + u * py;
-  out[5] = -a * n.z * py - u * px;
+  out[3] = k_fma(k_fma(an, n.z, -b), cs, un * (cc - ss));
+  out[4] = k_fma(u, py, -an * px);
+  out[5] = k_fma(-an, py, -(u * px));
   if (NC > 6) {
     out[NC > 6 ? 6 : 0] = v * n.x;
     out[NC > 7 ? 7 : 0] = v * n.y;
@@ -463,30 +514,46 @@ __device__ __forceinline__ Quat<R> quat_cast(const Quat<double>& q) {
   return Quat<R>{(R)q.w, (R)q.x, (R)q.y, (R)q.z};
 }
 
-// Tally flush, wave-cooperative and deferred.  A lane that leaves a cell
-// stages (key, NC values) in its wavefront's LDS area (wave_stage); when the
-// area may not hold another full wavefront of entries, wave_drain adds all
-// staged entries to the tally: lane L adds component L % NC of entry L / NC,
-// so one atomic instruction covers 64 / NC whole cells.  Deferring matters on
-// gfx9: atomics without return still count in vmcnt, and the next density
-// load's wait (vmcnt(0)) would otherwise wait every iteration for the last
-// flush's read-modify-writes to reach memory; drained every few iterations,
-// that latency is exposed once per drain.  Both must be reached by all lanes
-// of the wavefront; `staged` is the same in every lane.
+// Tally flush, wave-cooperative and deferred.  A lane's tallied segment is
+// staged as (key, NC values) in its wavefront's LDS area (wave_stage), or,
+// when it lies in the cell of the lane's last entry and that is still there,
+// added to it (multiple scattering inside a thick cell costs no atomics);
+// when the area may not hold another full wavefront of entries, wave_drain
+// adds all staged entries to the tally: lane L adds component L % NC of entry
+// L / NC, so one atomic instruction covers 64 / NC whole cells.  Deferring
+// matters on gfx9: atomics without return still count in vmcnt, and the next
+// density load's wait (vmcnt(0)) would otherwise wait every iteration for the
+// last flush's read-modify-writes to reach memory; drained every few
+// iterations, that latency is exposed once per drain.  Both must be reached by
+// all lanes of the wavefront; `staged` is the same in every lane.
 template <int NC>
-__device__ __forceinline__ int wave_stage(bool need, int64_t key, const double acc[NC], double* sv, long long* sk,
-                                          int lane, int& staged) {
+__device__ __forceinline__ int wave_stage_new(bool need, int64_t key, const double acc[NC], double* sv, long long* sk,
+                                              int lane, int& staged, int& slot) {
   const unsigned long long mask = __ballot(need);
   if (mask == 0ull) return 0;
   if (need) {
-    const int r = staged + __popcll(mask & ((1ull << lane) - 1ull));
+    slot = staged + __popcll(mask & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int k = 0; k < NC; ++k) sv[r * NC + k] = acc[k];
-    sk[r] = key;
+    for (int k = 0; k < NC; ++k) sv[slot * NC + k] = acc[k];
+    sk[slot] = key;
   }
   const int n = __popcll(mask);
   staged += n;
   return n;
+}
+template <int NC, typename R>
+__device__ __forceinline__ int wave_stage(bool has, int64_t key, const R cc[NC], double* sv, long long* sk, int lane,
+                                          int& staged, int64_t& last_key, int& slot) {
+  const bool same = has && slot >= 0 && key == last_key;
+  if (same) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) sv[slot * NC + k] += (double)cc[k];
+  }
+  double v[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) v[k] = (double)cc[k];
+  if (has) last_key = key;
+  return wave_stage_new<NC>(has && !same, key, v, sv, sk, lane, staged, slot);
 }
 
 template <int NC, int TS>
@@ -527,14 +594,47 @@ __device__ __forceinline__ void wave_drain(double* tally, double* sv, long long*
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Spherical grains' scattering in real arithmetic: the Jones matrix J_ij =
+// f_i . e_j of a proposal (e_i the bases of the incident direction, f_i of the
+// proposed one), the intensity it scatters from the incident coherency
+// (r11, r22, r12) divided by pf, and the scattered state.  Circular polarisation does
+// not arise (reals only).  As in coherency(), every rounding is written out.
+template <typename R>
+struct SphereJones {
+  R J11, J12, J21, J22;
+  __device__ __forceinline__ R set(R mu, R smu, R cph, R sph, R cpn, R spn, R stn, R nz, R r11, R r22, R r12) {
+#pragma clang fp contract(off)
+    const R e1x = nz * cpn, e1y = nz * spn;
+    const R f1x = mu * cph, f1y = mu * sph;
+    J11 = k_fma(stn, smu, k_fma(e1x, f1x, e1y * f1y));
+    J12 = k_fma(cpn, f1y, -(spn * f1x));
+    J21 = k_fma(e1y, cph, -(e1x * sph));
+    J22 = k_fma(cpn, cph, spn * sph);
+    const R C = k_fma(J21, J22, J11 * J12);
+    const R A = k_fma(J21, J21, J11 * J11), B = k_fma(J22, J22, J12 * J12);
+    return k_fma(r12, C + C, k_fma(r11, A, r22 * B));
+  }
+  // (I, Q, U) scattered, times pf, from the incident coherency
+  __device__ __forceinline__ void state(R pf, R r11, R r22, R r12, R& So, R& Qo, R& Uo) const {
+#pragma clang fp contract(off)
+    const R T11 = k_fma(r11, J11, r12 * J12), T12 = k_fma(r22, J12, r12 * J11);
+    const R T21 = k_fma(r11, J21, r12 * J22), T22 = k_fma(r22, J22, r12 * J21);
+    const R p11 = J11 * T11 + J12 * T12, p22 = J21 * T21 + J22 * T22;
+    const R p12 = J21 * T11 + J22 * T12;
+    So = (p22 + p11) * pf;
+    Qo = (p11 - p22) * pf;
+    Uo = (pf + pf) * p12;
+  }
+};
+
 // Scattering event (Sec. 2.2; rejection sampling of Sec. 3): incident state
 // carried into the grain frame, proposals uniform on the sphere there
 // (cos, azimuth, acceptance: three uniforms per trial), accepted when
 // u * bound <= [P s]_I, output rescaled to the scattered power, then carried
 // back to the lab frame.  Returns false on a numerical failure.
 template <typename R, bool ALIGNED, bool SPHERE>
-__device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
-                        const DustDev& D, uint64_t seed) {
+__device__ bool scatter(Packet<R>& p, const ColdRef& k, const Quat<R>& q, const Quat<double>& qd,
+                        const DustDev& D, uint64_t seed, float& u_tau) {
   const V3<R> n{(R)p.nx, (R)p.ny, (R)p.nz};
   V3<R> ng = n;
   R c2 = (R)1, s2 = (R)0;
@@ -556,7 +656,8 @@ __device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
   } else {
     azimuth(ng, cpn, spn, stn);
   }
-  const R I = p.I, Qg = c2 * p.Q + s2 * p.U, Ug = -s2 * p.Q + c2 * p.U, V = p.V;
+  const R I = p.I, V = p.V;
+  const R Qg = ALIGNED ? c2 * p.Q + s2 * p.U : p.Q, Ug = ALIGNED ? -s2 * p.Q + c2 * p.U : p.U;
   V3<R> e1, e2;
   e1 = {ng.z * cpn, ng.z * spn, -stn};
   e2 = {-spn, cpn, (R)0};
@@ -568,26 +669,30 @@ __device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
   const Cx<R> ap{(R)D.ap_re, (R)D.ap_im};
   const Cx<R> dd{(R)(D.aa_re - D.ap_re), (R)(D.aa_im - D.ap_im)};
   Cx<R> J11, J12, J21, J22;
+  SphereJones<R> js;
   R mu = 0, smu = 0, cph = 1, sph = 0, Iout = 0, umu = 0, uph = 0;
   bool ok = false;
-  for (int trial = 0; trial < 100000; ++trial) {
-    umu = next_uniform(p, seed);
+  uint32_t d = k.draw();
+  int trial = 0;
+  for (; trial < 100000; ++trial) {
+    float u[4];  // a trial's three, and the depth's once it is accepted
+    next_four(k, d, seed, p.lam, u);
+    d += 3;
+    umu = (R)u[0];
     mu = (R)2 * umu - (R)1;
-    uph = next_uniform(p, seed);
-    R ua = next_uniform(p, seed);
-    p.trials++;
+    uph = (R)u[1];
+    R ua = (R)u[2];
+    u_tau = u[3];
     // 1 - mu^2 as (1 - mu)(1 + mu): both factors are exact, so sin theta'
     // keeps full relative precision near the grain axis in FP32
     smu = sizeof(R) == 4 ? k_sqrt(fmax((R)0, ((R)1 - mu) * ((R)1 + mu))) : k_sqrt(fmax((R)0, (R)1 - mu * mu));
     k_sincospi((R)2 * uph, &sph, &cph);
     if (smu * smu <= (R)KP_POLE2) { cph = (R)1; sph = (R)0; }
-    const V3<R> f1{mu * cph, mu * sph, -smu}, f2{-sph, cph, (R)0};
-    const R D11 = dot(f1, e1), D12 = dot(f1, e2), D21 = dot(f2, e1), D22 = dot(f2, e2);
     if (SPHERE) {
-      J11 = {D11, 0}; J12 = {D12, 0}; J21 = {D21, 0}; J22 = {D22, 0};
-      Iout = pf * ((D11 * D11 + D21 * D21) * r11 + (D12 * D12 + D22 * D22) * r22 +
-                   (R)2 * (D11 * D12 + D21 * D22) * r12.re);
+      Iout = js.set(mu, smu, cph, sph, cpn, spn, stn, ng.z, r11, r22, r12.re) * pf;
     } else {
+      const V3<R> f1{mu * cph, mu * sph, -smu}, f2{-sph, cph, (R)0};
+      const R D11 = dot(f1, e1), D12 = dot(f1, e2), D21 = dot(f2, e1), D22 = dot(f2, e2);
       J11 = cadd(cscale(ap, D11), cscale(dd, smu * stn));
       J12 = cscale(ap, D12);
       J21 = cscale(ap, D21);
@@ -595,21 +700,30 @@ __device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
       Iout = pf * (cabs2(J11) * r11 + cabs2(J12) * r22 + (R)2 * cmulc(cmul(J11, r12), J12).re +
                    cabs2(J21) * r11 + cabs2(J22) * r22 + (R)2 * cmulc(cmul(J21, r12), J22).re);
     }
-    if (!(Iout <= bound * ((R)1 + tol))) return false;
+    if (!(Iout <= bound * ((R)1 + tol))) { ++trial; break; }
     if (ua * bound <= Iout) { ok = true; break; }
   }
+  k.trials() += (uint32_t)trial + (ok ? 1u : 0u);
   if (!ok) return false;
+  k.draw() = d + 1;
   // full scattered state rho' = J rho J^dagger in the natural basis of mg
-  const Cx<R> r21{r12.re, -r12.im};
-  const Cx<R> T11 = cadd(cscale(J11, r11), cmul(J12, r21));
-  const Cx<R> T12 = cadd(cmul(J11, r12), cscale(J12, r22));
-  const Cx<R> T21 = cadd(cscale(J21, r11), cmul(J22, r21));
-  const Cx<R> T22 = cadd(cmul(J21, r12), cscale(J22, r22));
-  const R p11 = cmulc(T11, J11).re + cmulc(T12, J12).re;
-  const R p22 = cmulc(T21, J21).re + cmulc(T22, J22).re;
-  const Cx<R> p12 = cadd(cmulc(T11, J21), cmulc(T12, J22));
-  R So = pf * (p11 + p22), Qo = pf * (p11 - p22), Uo = pf * (R)2 * p12.re,
+  R So, Qo, Uo, Vo = (R)0;
+  if (SPHERE) {
+    js.state(pf, r11, r22, r12.re, So, Qo, Uo);
+  } else {
+    const Cx<R> r21{r12.re, -r12.im};
+    const Cx<R> T11 = cadd(cscale(J11, r11), cmul(J12, r21));
+    const Cx<R> T12 = cadd(cmul(J11, r12), cscale(J12, r22));
+    const Cx<R> T21 = cadd(cscale(J21, r11), cmul(J22, r21));
+    const Cx<R> T22 = cadd(cmul(J21, r12), cscale(J22, r22));
+    const R p11 = cmulc(T11, J11).re + cmulc(T12, J12).re;
+    const R p22 = cmulc(T21, J21).re + cmulc(T22, J22).re;
+    const Cx<R> p12 = cadd(cmulc(T11, J21), cmulc(T12, J22));
+    So = pf * (p11 + p22);
+    Qo = pf * (p11 - p22);
+    Uo = pf * (R)2 * p12.re;
     Vo = pf * (R)-2 * p12.im;
+  }
   // scattered power: sum_k |a_k|^2 C_kk / N_P with C_zz = r11 sin^2(theta'_n)
   R sig = I;
   if (!SPHERE) {
@@ -624,7 +738,7 @@ __device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
     // outside |P| <= I (one packet of 1.5e8 on a 256^3 disk: |P| = 1.0008 I,
     // after which the next event's bound check fails); it is projected back
     // onto the cone.
-    const R p2 = Qo * Qo + Uo * Uo + Vo * Vo;
+    const R p2 = k_fma(Vo, Vo, k_fma(Qo, Qo, Uo * Uo));
     if (p2 > So * So) {
       const R f = So / k_sqrt(p2);
       Qo *= f; Uo *= f; Vo *= f;
@@ -645,7 +759,7 @@ __device__ bool scatter(Packet<R>& p, const Quat<R>& q, const Quat<double>& qd,
   }
   p.nx = md.x; p.ny = md.y; p.nz = md.z;
   p.rnx = 1.0 / p.nx; p.rny = 1.0 / p.ny; p.rnz = 1.0 / p.nz;
-  p.e_scat += (double)(sig - I);
+  k.e_scat() += (double)(sig - I);
   p.I = So;
   p.Q = cm * Qo - sm * Uo;
   p.U = sm * Qo + cm * Uo;
@@ -725,7 +839,7 @@ __device__ __forceinline__ void tab_toward(const DustDev& D, const V3<double>& n
 // <= the scattered I.  The total scattered power does not depend on the
 // polarisation, so the scattered state is rescaled to the incident I.
 template <typename R>
-__device__ bool scatter_tab(Packet<R>& p, const DustDev& D, uint64_t seed) {
+__device__ bool scatter_tab(Packet<R>& p, const ColdRef& k, const DustDev& D, uint64_t seed, float& u_tau) {
   const V3<double> n{p.nx, p.ny, p.nz};
   V3<double> th, ph;
   basis(n, th, ph);
@@ -735,9 +849,11 @@ __device__ bool scatter_tab(Packet<R>& p, const DustDev& D, uint64_t seed) {
   const double* cum = D.tab_cum;
   const double total = cum[nt - 1];
   for (int trial = 0; trial < 100000; ++trial) {
-    const double u1 = (double)next_uniform(p, seed), u2 = (double)next_uniform(p, seed);
-    const double u3 = (double)next_uniform(p, seed), u4 = (double)next_uniform(p, seed);
-    p.trials++;
+    float u[4];
+    next_four(k, k.draw(), seed, p.lam, u);
+    k.draw() += 4;
+    k.trials()++;
+    const double u1 = (double)u[0], u2 = (double)u[1], u3 = (double)u[2], u4 = (double)u[3];
     // the first interval whose cumulative envelope mass exceeds u1 * total
     const double target = u1 * total;
     int lo = 0, hi = nt - 2;
@@ -767,34 +883,33 @@ __device__ bool scatter_tab(Packet<R>& p, const DustDev& D, uint64_t seed) {
       p.nx = m.x; p.ny = m.y; p.nz = m.z;
       p.rnx = 1.0 / p.nx; p.rny = 1.0 / p.ny; p.rnz = 1.0 / p.nz;
       const R Io = (R)(o[0] * scale);
-      p.e_scat += (double)(Io - p.I);
+      k.e_scat() += (double)(Io - p.I);
       p.I = Io;
       p.Q = (R)(o[1] * scale);
       p.U = (R)(o[2] * scale);
       p.V = (R)(o[3] * scale);
+      u_tau = next_uniform(k, seed, p.lam);
       return true;
     }
   }
   return false;
 }
 
-template <bool MESH, typename R>
-__device__ uint32_t roulette(Packet<R>& p, const TransportArgs& a);
-
 // One loop iteration: one cell segment (Sec. 2.2: cell-to-cell traversal,
 // exponential scattering depth, continuous extinction across the segment by
 // the analytic cell solution of Appendix A, tally of the segment into the
 // scattering source of Sec. 2.3), then a scattering event or the crossing
-// into the next cell, then Russian roulette.  Returns 0 or an end kind.
+// into the next cell (Russian roulette follows in the caller).  Returns 0 or
+// an end kind.
 template <typename R, bool ALIGNED, bool SPHERE, bool TAB, bool MESH>
-__device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_t& key,
+__device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a, bool& has, int64_t& key,
                          R cc[TallyShape<SPHERE>::NC], bool& pending) {
   constexpr int NC = TallyShape<SPHERE>::NC;
   static_assert(!TAB || (SPHERE && !ALIGNED), "tabulated grains have scalar extinction");
   const uint64_t c = cell_index<MESH>(p, a);
-  p.last = (int64_t)c;
+  p.last = (uint32_t)c;
   if (p.events >= a.max_events || p.steps >= KP_MAX_STEPS) {
-    p.hash = hash_event(p.hash, END_BUDGET, c);
+    kc.hash() = hash_event(kc.hash(), END_BUDGET, c);
     return END_BUDGET;
   }
   const double inf = __builtin_huge_val();
@@ -828,13 +943,15 @@ __device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_
   if (rho > (R)0 && tl > (R)0) {
     const V3<R> n{(R)p.nx, (R)p.ny, (R)p.nz};
     const R Ib = p.I;
-    R JI, JQ, JU, JV;
+    R JI, JQ, JU, JV, Jp, Jm;  // Jp, Jm: J_I + J_Q, J_I - J_Q
     if (SPHERE && !ALIGNED) {
       // spheres: extinction is the scalar absorption e^{-rho kappa_abs l}
       const R m1 = rho * p.ka;
       const R E = k_exp(-m1 * tl), G = tl * phi1(m1 * tl);
       p.tau_path += m1 * tl;
       JI = p.I * G; JQ = p.Q * G; JU = p.U * G; JV = p.V * G;
+      Jp = k_fma(p.I, G, JQ);
+      Jm = k_fma(p.I, G, -JQ);
       p.I *= E; p.Q *= E; p.U *= E; p.V *= E;
     } else {
       // The exponents are differences of two cell-scale optical depths
@@ -880,6 +997,8 @@ __device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_
       JQ = c2 * JQg - s2 * JUg;
       JU = s2 * JQg + c2 * JUg;
       JV = JVg;
+      Jp = JI + JQ;
+      Jm = JI - JQ;
       p.I = (R)0.5 * (An + Bn);
       p.Q = c2 * Qn - s2 * Un;
       p.U = s2 * Qn + c2 * Un;
@@ -892,7 +1011,7 @@ __device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_
         // basis of n), projected on every camera when it is flushed
         cc[0] = JI * kb; cc[1] = JQ * kb; cc[2] = JU * kb; cc[3] = JV * kb;
       } else {
-        coherency<R, NC>(n, JI, JQ, JU, JV, kb, cc);
+        coherency<R, NC>(n, Jp, Jm, JU, JV, kb, cc);
       }
       key = (int64_t)((uint64_t)p.lam * a.nslot + sl);
       has = true;
@@ -902,7 +1021,7 @@ __device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_
     // the weight underflowed in a very thick absorbing segment: the packet is
     // absorbed (a non-finite weight is reported as a numerical failure)
     if (!isfinite(p.I)) return END_NUMERIC;
-    p.hash = hash_event(p.hash, END_RR_KILL, c);
+    kc.hash() = hash_event(kc.hash(), END_RR_KILL, c);
     return END_RR_KILL;
   }
   if (scat) {
@@ -942,13 +1061,13 @@ __device__ uint32_t step(Packet<R>& p, const TransportArgs& a, bool& has, int64_
     }
     if (MESH && out) out = mesh_cross(p, a);
     if (out) {
-      p.hash = hash_event(p.hash, END_ESCAPE, c);
+      kc.hash() = hash_event(kc.hash(), END_ESCAPE, c);
       return END_ESCAPE;
     }
     // the next step's density, in flight while this iteration finishes
     if (!TallyShape<SPHERE>::HAS_B) p.rho = a.rho[cell_index<MESH>(p, a)];
   }
-  return roulette<MESH>(p, a);
+  return 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1052,7 +1171,7 @@ __device__ void peel_off(const Packet<R>& p, const TransportArgs& a, const Quat<
                          const DustDev& D) {
   double C9[9];
   const double s_in[4] = {(double)p.I, (double)p.Q, (double)p.U, (double)p.V};
-  if (!TAB) coherency<double, 9>(V3<double>{p.nx, p.ny, p.nz}, s_in[0], s_in[1], s_in[2], s_in[3], 1.0, C9);
+  if (!TAB) coherency<double, 9>(V3<double>{p.nx, p.ny, p.nz}, s_in[0] + s_in[1], s_in[0] - s_in[1], s_in[2], s_in[3], 1.0, C9);
   double X[3] = {a.x0 + ((double)p.ci + p.fx) * a.dx, a.y0 + ((double)p.cj + p.fy) * a.dx,
                  a.z0 + ((double)p.ck + p.fz) * a.dx};
   if (MESH) {
@@ -1213,9 +1332,9 @@ __device__ void wave_drain_views(const TransportArgs& a, double* sv, long long* 
 }
 
 // Scattering event at the packet's current position (Sec. 2.2), the next
-// scattering depth, and the roulette check that follows every segment.
+// scattering depth.
 template <typename R, bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
-__device__ uint32_t scatter_step(Packet<R>& p, const TransportArgs& a) {
+__device__ uint32_t scatter_step(Packet<R>& p, const ColdRef& k, const TransportArgs& a) {
   const uint64_t c = cell_index<MESH>(p, a);
   const DustDev& D = a.dust[p.lam];
   Quat<R> q{(R)1, (R)0, (R)0, (R)0};
@@ -1228,33 +1347,34 @@ __device__ uint32_t scatter_step(Packet<R>& p, const TransportArgs& a) {
     q = quat_cast<R>(qd);
   }
   if (PEEL) peel_off<R, ALIGNED, SPHERE, TAB, MESH>(p, a, qd, D);
+  float u_tau;
   if (TAB) {
-    if (!scatter_tab<R>(p, D, a.seed)) return END_NUMERIC;
-  } else if (!scatter<R, ALIGNED, SPHERE>(p, q, qd, D, a.seed)) {
+    if (!scatter_tab<R>(p, k, D, a.seed, u_tau)) return END_NUMERIC;
+  } else if (!scatter<R, ALIGNED, SPHERE>(p, k, q, qd, D, a.seed, u_tau)) {
     return END_NUMERIC;
   }
   p.events++;
-  p.hash = hash_event(p.hash, EV_SCATTER, c);
-  p.tau = -log((double)next_uniform(p, a.seed));
-  return roulette<MESH>(p, a);
+  k.hash() = hash_event(k.hash(), EV_SCATTER, c);
+  p.tau = -log((double)u_tau);
+  return 0;
 }
 
 // Russian roulette after a segment or an event in the packet's cell (reading
 // R8); the cell index is formed only when the check draws
 template <bool MESH, typename R>
-__device__ uint32_t roulette(Packet<R>& p, const TransportArgs& a) {
+__device__ uint32_t roulette(Packet<R>& p, const ColdRef& k, const TransportArgs& a) {
   if (!isfinite(p.I)) return END_NUMERIC;
   if (a.rr_wmin > 0.0 && p.I < (R)a.rr_wmin * p.w0) {
     const uint64_t cn = cell_index<MESH>(p, a);
-    R u = next_uniform(p, a.seed);
+    const R u = (R)next_uniform(k, a.seed, p.lam);
     if (u < (R)a.rr_psurv) {
       const R before = p.I, inv = (R)1 / (R)a.rr_psurv;
       p.I *= inv; p.Q *= inv; p.U *= inv; p.V *= inv;
-      p.e_gain += (double)(p.I - before);
-      p.rr++;
-      p.hash = hash_event(p.hash, EV_RR_SURVIVE, cn);
+      k.e_gain() += (double)(p.I - before);
+      k.rr()++;
+      k.hash() = hash_event(k.hash(), EV_RR_SURVIVE, cn);
     } else {
-      p.hash = hash_event(p.hash, END_RR_KILL, cn);
+      k.hash() = hash_event(k.hash(), END_RR_KILL, cn);
       return END_RR_KILL;
     }
   }
@@ -1266,17 +1386,17 @@ enum { SC_STEPS, SC_SCAT, SC_TRIALS, SC_KILL, SC_SURV, SC_ESC, SC_BUDGET, SC_NUM
 enum { SE_EMIT, SE_ESC, SE_ABS, SE_KILL, SE_GAIN, SE_BUDGET, SE_SCAT, SE_N };
 
 template <typename R>
-__device__ void finish(const Packet<R>& p, uint32_t end, const TransportArgs& a,
+__device__ void finish(const Packet<R>& p, const ColdRef& k, uint32_t end, const TransportArgs& a,
                        unsigned long long* sc, double* se) {
   atomicAdd(&sc[SC_STEPS], (unsigned long long)p.steps);
   atomicAdd(&sc[SC_SCAT], (unsigned long long)p.events);
-  atomicAdd(&sc[SC_TRIALS], (unsigned long long)p.trials);
+  atomicAdd(&sc[SC_TRIALS], (unsigned long long)k.trials());
   atomicAdd(&sc[SC_PACK], 1ull);
-  if (p.rr) atomicAdd(&sc[SC_SURV], (unsigned long long)p.rr);
+  if (k.rr()) atomicAdd(&sc[SC_SURV], (unsigned long long)k.rr());
   if (end != END_NUMERIC) {
     atomicAdd(&se[SE_ABS], p.e_abs);
-    atomicAdd(&se[SE_SCAT], p.e_scat);
-    if (p.e_gain != 0.0) atomicAdd(&se[SE_GAIN], p.e_gain);
+    atomicAdd(&se[SE_SCAT], k.e_scat());
+    if (k.e_gain() != 0.0) atomicAdd(&se[SE_GAIN], k.e_gain());
   }
   switch (end) {
     case END_ESCAPE: atomicAdd(&sc[SC_ESC], 1ull); atomicAdd(&se[SE_ESC], (double)p.I); break;
@@ -1284,19 +1404,33 @@ __device__ void finish(const Packet<R>& p, uint32_t end, const TransportArgs& a,
     case END_BUDGET: atomicAdd(&sc[SC_BUDGET], 1ull); atomicAdd(&se[SE_BUDGET], (double)p.I); break;
     default: atomicAdd(&sc[SC_NUM], 1ull); break;
   }
-  if (a.trace_count && (p.pid % a.trace_stride) == 0 && p.pid / a.trace_stride < a.trace_count) {
-    TraceDev& t = a.traces[(uint64_t)p.lam * a.trace_count + p.pid / a.trace_stride];
-    t.packet = p.pid;
+  const uint64_t pid = k.pid();
+  if (a.trace_count && (pid % a.trace_stride) == 0 && pid / a.trace_stride < a.trace_count) {
+    TraceDev& t = a.traces[(uint64_t)p.lam * a.trace_count + pid / a.trace_stride];
+    t.packet = pid;
     t.end_kind = (int32_t)end;
     t.events = p.events;
     t.steps = p.steps;
-    t.last_cell = p.last;
+    t.last_cell = p.last == 0xffffffffu ? -1ll : (int64_t)p.last;
     t.n[0] = (double)p.nx; t.n[1] = (double)p.ny; t.n[2] = (double)p.nz;
     t.stokes[0] = (double)p.I; t.stokes[1] = (double)p.Q;
     t.stokes[2] = (double)p.U; t.stokes[3] = (double)p.V;
-    t.hash = p.hash;
+    t.hash = k.hash();
     t.tau_path = (double)p.tau_path;
   }
+}
+
+// The kernel's arguments read again from its argument segment, for the paths
+// that few iterations take (start, scattering, end of a packet): their
+// arguments are then loaded there instead of being held in scalar registers
+// (and spilled to vector ones) through the whole loop.
+__device__ __forceinline__ TransportArgs reload_args(int varying) {
+  const __attribute__((address_space(4))) char* p =
+      (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p) : "s"(varying));
+  TransportArgs r;
+  __builtin_memcpy(&r, p, sizeof r);
+  return r;
 }
 
 template <typename R, bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
@@ -1304,20 +1438,21 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   constexpr int NC = TallyShape<SPHERE>::NC, TS = TallyShape<SPHERE>::TS;
   __shared__ unsigned long long sc[SC_N];
   __shared__ double se[SE_N];
-  // flush staging, one area of FLUSH_CAP entries per wavefront (43 KB per
-  // block for spheres, 61 KB for aligned grains: two blocks per CU; 32 KB
-  // for tabulated grains, whose entries are the segment's Stokes integral and
-  // direction, 7 values).  A wavefront drains its area once it holds more
-  // than FLUSH_CAP - 64 entries (a stage adds at most 64), so a drain covers
-  // FLUSH_CAP - 63 .. FLUSH_CAP entries.  With the tally in bricks a cap of
-  // 192 beat 256 on the 256^3 disk: 726.8 vs 737.9 ms (a cap of 128:
-  // 729.2 ms).
+  // flush staging, one area of FLUSH_CAP entries per wavefront (28 KB per
+  // block for spheres, 41 KB for aligned grains; tabulated grains' entries are
+  // the segment's Stokes integral and direction, 7 values).  A wavefront
+  // drains its area once it holds more than FLUSH_CAP - 64 entries (a stage
+  // adds at most 64).  With the cold state (21 KB) three blocks of spheres and two
+  // of aligned grains fit a CU; caps of 96 and 150 measured 1-3 % and 5 % slower on
+  // the disk.
   constexpr int NSV = TAB ? 7 : NC;
-  constexpr int FLUSH_CAP = TAB ? 128 : 192;
+  constexpr int FLUSH_CAP = 128;
+  static_assert(FLUSH_CAP > 64, "an area must take a wavefront's entries");
   __shared__ double s_val[4 * FLUSH_CAP * NSV];
   // tabulated grains: per wavefront the projections of one drain round
   __shared__ double s_proj[TAB ? 4 * 256 : 1];
   __shared__ long long s_key[4 * FLUSH_CAP];
+  __shared__ Cold s_cold[4];
   if (threadIdx.x < SC_N) sc[threadIdx.x] = 0ull;
   if (threadIdx.x < SE_N) se[threadIdx.x] = 0.0;
   __syncthreads();
@@ -1327,15 +1462,14 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   double* sv = s_val + wv * FLUSH_CAP * NSV;
   double* sp = s_proj + (TAB ? wv * 256 : 0);
   long long* sk = s_key + wv * FLUSH_CAP;
+  const ColdRef kc{s_cold[wv], lane};
   int staged = 0;  // entries in this wavefront's staging area (uniform)
   Packet<R> p;
   bool active = false, exhausted = false, pending = false;
   int waited = 0;
-  int64_t acc_key = -1;
+  int64_t last_key = -1;  // key and staging slot of this lane's last entry (slot -1: drained)
+  int slot = -1;
   unsigned long long flushes = 0;  // tally cells flushed by this wavefront
-  double acc[NC];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) acc[k] = 0.0;
 
   // Packet ids reserved by this wavefront, [wnext, wend) (uniform).  With
   // spherical grains a step is short and every wavefront refills its idle
@@ -1347,99 +1481,89 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   // take exactly the ids they need.
   constexpr bool CHUNKED = SPHERE;
   constexpr unsigned long long WAVE_CHUNK = 64;
+  // Lanes refilled together: a start costs ~900 instructions (Philox, sines, a
+  // logarithm, divisions) whatever the number of lanes that run it.  1, 8 and 16
+  // lanes: aligned slab 39.6, 33.6, 27.3 ms; aligned disk 15.0, 13.7, 13.8;
+  // spherical disk within 1 %.
+  constexpr int REFILL_BATCH = 8;
   // a refill hands up to 64 idle lanes ids from one new chunk
   static_assert(WAVE_CHUNK >= 64, "a chunk must cover a whole wavefront");
   unsigned long long wnext = 0, wend = 0;
   bool global_done = false;  // the global counter has passed the total
+  uint32_t ended = 0;        // this lane's packet has ended (its end kind), not yet reported
   while (true) {
-    // refill idle lanes; a chunked wavefront keeps refilling while it holds no
-    // packet and still reserves ids (all it was handed may have left the grid)
-    do {
-    if (!exhausted) {
-      const unsigned long long idle = __ballot(!active);
-      if (idle) {
-        const unsigned long long nidle = (unsigned long long)__popcll(idle);
-        const int leader = __ffsll((unsigned long long)idle) - 1;
-        if (CHUNKED) {
-          const unsigned long long rem = wend - wnext;
-          const bool refill = rem < nidle && !global_done;
-          unsigned long long base = 0;
-          if (refill) {
-            if (lane == leader) base = atomicAdd(a.counter, WAVE_CHUNK);
-            // the leader's value, as a wave-uniform (scalar) value
-            const unsigned lo = __builtin_amdgcn_readlane((unsigned)base, leader);
-            const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), leader);
-            base = ((unsigned long long)hi << 32) | lo;
-            if (base + WAVE_CHUNK >= a.total) global_done = true;
-          }
-          if (!active) {
-            const unsigned long long r = (unsigned long long)__popcll(idle & ((1ull << lane) - 1ull));
-            const bool have = r < rem || refill;
-            const unsigned long long g = r < rem ? wnext + r : base + (r - rem);
-            if (have && g < a.total) {
-              const bool in = init_packet<R, ALIGNED, SPHERE, MESH>(p, g, a);
-              atomicAdd(&se[SE_EMIT], (double)p.I);  // the emitted intensity
-              if (in) active = true;
-              else finish(p, END_ESCAPE, a, sc, se);
-            }
-          }
-          if (refill) {
-            wnext = base + (nidle - rem);
-            wend = base + WAVE_CHUNK;
-          } else {
-            wnext += nidle < rem ? nidle : rem;
-          }
-          if (global_done && (wnext >= wend || wnext >= a.total)) exhausted = true;
-        } else {
-          unsigned long long base = 0;
-          if (lane == leader) base = atomicAdd(a.counter, nidle);
-          base = __shfl(base, leader);
-          if (!active) {
-            const unsigned long long below = idle & ((1ull << lane) - 1ull);
-            const unsigned long long g = base + (unsigned long long)__popcll(below);
-            if (g < a.total) {
-              const bool in = init_packet<R, ALIGNED, SPHERE, MESH>(p, g, a);
-              atomicAdd(&se[SE_EMIT], (double)p.I);  // the emitted intensity
-              if (in) active = true;
-              else finish(p, END_ESCAPE, a, sc, se);
-            }
-          }
-          if (base + nidle >= a.total) exhausted = true;
-        }
+    // Ended packets are reported (finish) and their lanes refilled for
+    // REFILL_BATCH lanes of the wavefront at a time, or when no lane is left to
+    // move: both run once for all of them instead of once per packet.
+    const int nactive = __popcll(__ballot(active));
+    if (nactive == 0 || (!exhausted && 64 - nactive >= REFILL_BATCH)) {
+      if (ended) {
+        finish(p, kc, ended, reload_args(nactive), sc, se);
+        ended = 0;
       }
+      if (exhausted) break;  // nothing moves (nactive == 0) and no ids are left
+      const unsigned long long idle = __ballot(!active);
+      const unsigned long long nidle = (unsigned long long)__popcll(idle);
+      const int leader = __ffsll((unsigned long long)idle) - 1;
+      bool have;
+      unsigned long long g;
+      const unsigned long long r = (unsigned long long)__popcll(idle & ((1ull << lane) - 1ull));
+      if (CHUNKED) {
+        const unsigned long long rem = wend - wnext;
+        const bool refill = rem < nidle && !global_done;
+        unsigned long long base = 0;
+        if (refill) {
+          if (lane == leader) base = atomicAdd(a.counter, WAVE_CHUNK);
+          // the leader's value, as a wave-uniform (scalar) value
+          const unsigned lo = __builtin_amdgcn_readlane((unsigned)base, leader);
+          const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), leader);
+          base = ((unsigned long long)hi << 32) | lo;
+          if (base + WAVE_CHUNK >= a.total) global_done = true;
+        }
+        have = r < rem || refill;
+        g = r < rem ? wnext + r : base + (r - rem);
+        if (refill) {
+          wnext = base + (nidle - rem);
+          wend = base + WAVE_CHUNK;
+        } else {
+          wnext += nidle < rem ? nidle : rem;
+        }
+        if (global_done && (wnext >= wend || wnext >= a.total)) exhausted = true;
+      } else {
+        unsigned long long base = 0;
+        if (lane == leader) base = atomicAdd(a.counter, nidle);
+        base = __shfl(base, leader);
+        have = true;
+        g = base + r;
+        if (base + nidle >= a.total) exhausted = true;
+      }
+      if (!active && have && g < a.total) {
+        const bool in = init_packet<R, ALIGNED, SPHERE, MESH>(p, kc, g, reload_args(nactive));
+        atomicAdd(&se[SE_EMIT], (double)p.I);  // the emitted intensity
+        if (in) active = true;
+        else ended = END_ESCAPE;
+      }
+      continue;
     }
-    } while (CHUNKED && !exhausted && !__any(active));
-    if (!__any(active)) break;
-    bool has = false;
+    bool has = false, check = false;
     int64_t key = -1;
     R cc[NC];
     if (active && !pending) {
-      const uint32_t end = step<R, ALIGNED, SPHERE, TAB, MESH>(p, a, has, key, cc, pending);
-      if (end) {
-        finish(p, end, a, sc, se);
-        active = false;
-      }
+      ended = step<R, ALIGNED, SPHERE, TAB, MESH>(p, kc, a, has, key, cc, pending);
+      check = !ended && !pending;
     }
     if (TAB) {
       // tabulated grains: every segment is staged with its direction (a
       // segment's projection on the cameras depends on it)
       const double e7[7] = {(double)cc[0], (double)cc[1], (double)cc[2], (double)cc[3], p.nx, p.ny, p.nz};
-      flushes += wave_stage<7>(has, key, e7, sv, sk, lane, staged);
+      flushes += wave_stage_new<7>(has, key, e7, sv, sk, lane, staged, slot);
       if (staged > FLUSH_CAP - 64) wave_drain_views<MESH>(a, sv, sk, sp, lane, staged);
     } else {
-    // a lane entering another (wavelength, cell) hands its running sum over
-    flushes += wave_stage<NC>(has && key != acc_key && acc_key >= 0, acc_key, acc, sv, sk, lane, staged);
-    if (staged > FLUSH_CAP - 64) wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
-    if (has) {
-      if (key == acc_key) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k) acc[k] += (double)cc[k];
-      } else {
-        acc_key = key;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) acc[k] = (double)cc[k];
+      flushes += wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
+      if (staged > FLUSH_CAP - 64) {
+        wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
+        slot = -1;
       }
-    }
     }
     // Scattering events are run for the parked lanes together once enough
     // of them wait (or one has waited long enough, or nothing else can
@@ -1448,47 +1572,51 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     const unsigned long long pm = __ballot(pending);
     if (pm) {
       ++waited;
-      const unsigned long long movable = __ballot(active && !pending);
+      const unsigned long long movable = __ballot(active && !ended && !pending);
       if (__popcll(pm) >= a.scatter_batch || waited >= a.scatter_wait || movable == 0ull) {
         waited = 0;
         if (pending) {
           pending = false;
-          const uint32_t end = scatter_step<R, ALIGNED, SPHERE, PEEL, TAB, MESH>(p, a);
-          if (end) {
-            finish(p, end, a, sc, se);
-            active = false;
-          }
+          ended = scatter_step<R, ALIGNED, SPHERE, PEEL, TAB, MESH>(p, kc, reload_args(nactive));
+          check = !ended;
         }
       }
     }
+    if (check) ended = roulette<MESH>(p, kc, a);
+    if (ended) active = false;
   }
-  if (TAB) {
-    wave_drain_views<MESH>(a, sv, sk, sp, lane, staged);
-  } else {
-    flushes += wave_stage<NC>(acc_key >= 0, acc_key, acc, sv, sk, lane, staged);
-    wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
-  }
+  if (TAB) wave_drain_views<MESH>(a, sv, sk, sp, lane, staged);
+  else wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
   if (lane == 0) atomicAdd(&sc[SC_FLUSH], flushes);
   __syncthreads();
   if (threadIdx.x < SC_N) atomicAdd(&(&a.stats->cell_steps)[threadIdx.x], sc[threadIdx.x]);
   if (threadIdx.x < SE_N) unsafeAtomicAdd(&(&a.stats->e_emitted)[threadIdx.x], se[threadIdx.x]);
 }
 
-// The persistent transport kernels.  FP32 variants are held to two waves per
-// SIMD (at most 256 registers): the non-spherical FP32 bodies need 264-272
-// unconstrained and would run one wave per SIMD; the bound costs them about a
-// dozen spills and makes them 1.5x faster.  The FP64 variants need 297-361;
-// holding them to two waves spills 50-190 registers and halves their speed,
-// so they run unbounded at one wave per SIMD.  PEEL adds peel-off imaging at
-// every scattering event (a separate instantiation: the kernels without it
-// are unchanged).
+// The persistent transport kernels.  VALU issue and its latency bound them
+// (disk: VALU busy 0.72 of the cycles at two waves per SIMD, aligned grains
+// 0.45 at one), beside the L2's line atomics, so registers are what the body is
+// written for: with the rarely touched state in LDS (Cold), the arguments of
+// the rare paths read again where they are used (reload_args) and machine
+// LICM off (it would hold the literals of every path in registers across the
+// loop), the sphere kernel takes 125 registers (253 before), tables 185, the mesh
+// 161 and the FP64 kernel of aligned grains 200 (361), none with a spill:
+// three waves per SIMD for spheres and the mesh and two for aligned grains in FP64
+// (which spilled 50-190 registers at two before).  256^3 disk, 1e6 packets:
+// 8.44 -> 7.17 ms, 3e7: 213.5 -> 173.0 ms; aligned grains, 1e6: 21.9 -> 13.4 ms;
+// refined sphere, 2e6: 37.3 -> 31.7 ms.  Four waves per SIMD for spheres measured
+// 7.29 / 177.7 ms, and any spill costs more than a wave gains (47 spilled
+// registers at four waves: 15.5 ms).  PEEL adds peel-off imaging at every
+// scattering event (a separate instantiation); its FP64 body keeps the
+// registers it needs, at one wave.
 template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_transport32(TransportArgs a) {
   transport_body<float, ALIGNED, SPHERE, PEEL, TAB, MESH>(a);
 }
 template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
-__global__ void __launch_bounds__(256) k_transport64(TransportArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PEEL ? 1 : 2)))
+k_transport64(TransportArgs a) {
   transport_body<double, ALIGNED, SPHERE, PEEL, TAB, MESH>(a);
 }
 
