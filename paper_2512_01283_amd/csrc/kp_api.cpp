@@ -354,10 +354,12 @@ TallyLayout tally_layout(const kp_ctx* ctx) {
 // Step 2.  With user_source the source is the per-view array d_S (the
 // caller's, or the per-view tally of tabulated grains when from_tally),
 // else the coherency tally d_tally; the dust's thermal term is added for a
-// thermal source unless the caller supplied the source.
+// thermal source unless the caller supplied the source.  same_call: step 1 ran
+// in this call, so the grain frames in the tally's blocks are those of the
+// alignment array (which its owner may change between calls).
 kp_status image_launch(kp_ctx* ctx, bool user_source, const double* d_S, double* d_out,
                        int n_lambda, hipStream_t s, const DustDev* d_dust, const ViewDev* d_views,
-                       const double* d_tally, bool from_tally = false) {
+                       const double* d_tally, bool same_call, bool from_tally = false) {
   ImageArgs a{};
   a.rho = ctx->d_rho;
   if (ctx->d_bhat) {
@@ -386,6 +388,7 @@ kp_status image_launch(kp_ctx* ctx, bool user_source, const double* d_S, double*
   a.tby = slots ? tl.tby : 0;
   a.em_B = ((!user_source || from_tally) && ctx->src.kind == 2) ? ctx->d_em_B : nullptr;
   a.boundary = ctx->grid.boundary;
+  a.axis_in_tally = same_call && d_tally ? 1 : 0;
   a.mesh = mesh_dev(ctx);
   // every wavelength shares the grain model kind of wavelength 0 for the
   // kernel choice; mixed sphere / non-sphere tables use the general kernel
@@ -982,7 +985,8 @@ kp_status kp_transport(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, vo
   return st;
 }
 
-kp_status kp_image(kp_ctx* ctx, void* stream) {
+// kp_image; same_call: from kp_run, right after its step 1
+static kp_status image_step(kp_ctx* ctx, bool same_call, void* stream) {
   if (!ctx) return KP_ERR_ARG;
   if (!ctx->have_tally) return fail(ctx, KP_ERR_STATE, "no step-1 tally: call kp_transport first");
   kp_status st = check_ready(ctx);
@@ -996,9 +1000,10 @@ kp_status kp_image(kp_ctx* ctx, void* stream) {
   if (ctx->tally_views) {
     if (!ctx->have_tables || ctx->tally_nv != (int)ctx->views.size())
       return fail(ctx, KP_ERR_STATE, "the per-view tally no longer matches the dust tables or cameras");
-    st = image_launch(ctx, true, ctx->d_tally, ctx->d_images, nl, s, ctx->d_dust, ctx->d_views, nullptr, true);
+    st = image_launch(ctx, true, ctx->d_tally, ctx->d_images, nl, s, ctx->d_dust, ctx->d_views, nullptr, same_call,
+                      true);
   } else {
-    st = image_launch(ctx, false, nullptr, ctx->d_images, nl, s, ctx->d_dust, ctx->d_views, ctx->d_tally);
+    st = image_launch(ctx, false, nullptr, ctx->d_images, nl, s, ctx->d_dust, ctx->d_views, ctx->d_tally, same_call);
   }
   if (st) return st;
   KP_HIP(hipStreamSynchronize(s), "imaging kernel");
@@ -1010,10 +1015,12 @@ kp_status kp_image(kp_ctx* ctx, void* stream) {
   return KP_OK;
 }
 
+kp_status kp_image(kp_ctx* ctx, void* stream) { return image_step(ctx, false, stream); }
+
 kp_status kp_run(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, void* stream) {
   kp_status st = kp_transport(ctx, counts, o, stream);
   if (st != KP_OK && st != KP_ERR_NUMERIC && st != KP_ERR_BUDGET) return st;
-  kp_status st2 = kp_image(ctx, stream);
+  kp_status st2 = image_step(ctx, true, stream);
   return st2 != KP_OK ? st2 : st;
 }
 
@@ -1068,8 +1075,8 @@ kp_status kp_run_static(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, d
   st = transport_launch(ctx, o, total, buf, s);
   if (st == KP_ERR_DEVICE || st == KP_ERR_OOM) return st;
   kp_status st2 = ctx->have_tables
-                      ? image_launch(ctx, true, d_tally, d_images, nl, s, d_dust, d_views, nullptr, true)
-                      : image_launch(ctx, false, nullptr, d_images, nl, s, d_dust, d_views, d_tally);
+                      ? image_launch(ctx, true, d_tally, d_images, nl, s, d_dust, d_views, nullptr, true, true)
+                      : image_launch(ctx, false, nullptr, d_images, nl, s, d_dust, d_views, d_tally, true);
   if (st2) return st2;
   KP_HIP(hipStreamSynchronize(s), "imaging kernel");
   float ms = 0.0f;
@@ -1088,7 +1095,7 @@ kp_status kp_image_source(kp_ctx* ctx, const double* d_S, double* d_out, void* s
   std::vector<uint64_t> ones(ctx->dust.size(), 1);
   fill_dust(ctx, ones.data(), ctx->hdust);
   if ((st = upload_small(ctx, s))) return st;
-  if ((st = image_launch(ctx, true, d_S, d_out, 1, s, ctx->d_dust, ctx->d_views, ctx->d_tally))) return st;
+  if ((st = image_launch(ctx, true, d_S, d_out, 1, s, ctx->d_dust, ctx->d_views, nullptr, false))) return st;
   KP_HIP(hipStreamSynchronize(s), "imaging kernel");
   float ms = 0.0f;
   KP_HIP(hipEventElapsedTime(&ms, ctx->ev[2], ctx->ev[3]), "event timing");

@@ -145,6 +145,7 @@ struct ImageArgs {
   const float* em_B;    // [lambda][ncell] source function of the dust's thermal
                         // emission, or null (no thermal source term)
   int boundary;         // bit a: axis a periodic
+  int axis_in_tally;    // the tally's blocks hold the grain frames of these bx, by, bz
   MeshDev mesh;         // the kernels instantiated for a composite mesh
 };
 

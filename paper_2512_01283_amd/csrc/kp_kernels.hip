@@ -1,6 +1,6 @@
 // kp_kernels.hip -- gfx950 kernels of the polarized Monte Carlo transport
-// (step 1) and the deterministic imaging ray-march (step 2) of Yang & Wang,
-// arXiv:2512.01283, Sec. 2.2-2.3 and Appendix A.
+// (step 1) of Yang & Wang, arXiv:2512.01283, Sec. 2.2-2.3 and Appendix A (step 2
+// is in kp_image.hip).
 //
 // Step 1 is a persistent packet-per-lane loop: every lane of a 64-wide
 // wavefront carries one photon packet and advances it by one cell segment per
@@ -24,8 +24,7 @@
 // components of ~7-10 cells, each cell's block aligned to one cache line
 // (64 B for 6 reals, 128 B for 9) -- memory-side FP64 atomics are charged per
 // line request, so this is ~5x cheaper than one cell per lane.
-#include "kp_device.hpp"
-#include "kp_internal.hpp"
+#include "kp_transfer.hpp"
 
 namespace kp {
 
@@ -45,19 +44,6 @@ __device__ __forceinline__ uint64_t fnv_u32(uint64_t h, uint32_t v) {
 __device__ __forceinline__ uint64_t hash_event(uint64_t h, uint32_t kind, uint64_t cell) {
   return fnv_u32(fnv_u32(h, kind), (uint32_t)cell);
 }
-
-template <typename R> struct Cx { R re, im; };
-template <typename R> __device__ __forceinline__ Cx<R> cmul(Cx<R> a, Cx<R> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
-}
-template <typename R> __device__ __forceinline__ Cx<R> cmulc(Cx<R> a, Cx<R> b) {  // a * conj(b)
-  return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
-}
-template <typename R> __device__ __forceinline__ Cx<R> cadd(Cx<R> a, Cx<R> b) {
-  return {a.re + b.re, a.im + b.im};
-}
-template <typename R> __device__ __forceinline__ R cabs2(Cx<R> a) { return a.re * a.re + a.im * a.im; }
-template <typename R> __device__ __forceinline__ Cx<R> cscale(Cx<R> a, R s) { return {a.re * s, a.im * s}; }
 
 template <typename R>
 struct Packet {
@@ -140,19 +126,6 @@ __device__ __forceinline__ void next_four(const ColdRef& k, uint32_t d, uint64_t
   for (uint32_t i = 0; i < 4; ++i) u[i] = k.u(d + i);
 }
 
-// Dimensionless extinction coefficients for a direction with cos(theta') =
-// ct to the grain axis (dipole: cross sections from Im of the
-// polarizability, normalised by the orientation average).
-template <typename R, bool SPHERE>
-__device__ __forceinline__ void alphas(const DustDev& D, R ct, R& a1, R& a2, R& a3) {
-  if (SPHERE) { a1 = (R)1; a2 = (R)0; a3 = (R)0; return; }
-  R cth = (R)D.ap_im * ct * ct + (R)D.aa_im * (sizeof(R) == 4 ? ((R)1 - ct) * ((R)1 + ct) : (R)1 - ct * ct);
-  R cph = (R)D.ap_im;
-  a1 = (cth + cph) * (R)D.inv2cavg;
-  a2 = (cth - cph) * (R)D.inv2cavg;
-  a3 = (R)D.alpha3_scale * a2;
-}
-
 // Isotropic direction from two uniforms: mu = 2 u0 - 1, azimuth 2 pi u1.
 template <typename R>
 __device__ __forceinline__ void isotropic_dir(Packet<R>& p, double u0, double u1) {
@@ -179,49 +152,6 @@ __device__ __forceinline__ uint64_t emission_cell(const double* F, const uint32_
     if (t < F[mid]) hi = mid; else lo = mid + 1;
   }
   return lo;
-}
-
-// Emission (Sec. 2.2).  Point sources: isotropic direction (or the pencil
-// direction), an unpolarised Stokes vector of weight lum/N, and the cell
-// holding the source (a coordinate on a face belongs to the cell the
-// direction points into).  Thermal emission of the dust (the alpha_abs B
-// term of eq. polarized-rt): the cell drawn by luminosity 4 pi rho kappa_abs
-// B V, the position uniform in it, an isotropic direction and the Stokes
-// vector w (alpha1, alpha2, 0, 0) in the grain-frame basis of the direction
-// (the dichroism of absorption is that of extinction), carried to the lab
-// basis; its mean over directions is w.  Draws: cell, three coordinates,
-// two for the direction.  Then an exponential scattering depth.  Returns
-// false if a point source lies outside the grid.
-// ---------------------------------------------------------------------------
-// Composite mesh with static refinement (Sec. 2: the mesh the packets
-// cross).  Inside a leaf block the cell walk is the uniform one; leaving it,
-// the point is expressed in finest-cell units (exact on the crossed face,
-// since cell edges are powers of two of the finest one), its finest cell
-// taken with the face rule (a coordinate on a face belongs to the cell the
-// direction points into), and the leaf holding that cell found by
-// descending from its root block.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ long long finest_cell(double t, double n) {
-  const double fl = floor(t);
-  long long X = (long long)fl;
-  if (fl == t && n < 0.0) X -= 1;
-  return X;
-}
-
-__device__ __forceinline__ int mesh_find(const MeshDev& m, const long long X[3]) {
-  const long long full = (long long)m.block << m.max_level;
-  const long long r0 = X[0] / full, r1 = X[1] / full, r2 = X[2] / full;
-  int node = (int)(r0 + (long long)m.rx * (r1 + (long long)m.ry * r2));
-  long long o0 = r0 * full, o1 = r1 * full, o2 = r2 * full, size = full;
-  for (int c = m.child[node]; c >= 0; c = m.child[node]) {
-    size >>= 1;
-    int oct = 0;
-    if (X[0] - o0 >= size) { oct |= 1; o0 += size; }
-    if (X[1] - o1 >= size) { oct |= 2; o1 += size; }
-    if (X[2] - o2 >= size) { oct |= 4; o2 += size; }
-    node = c + oct;
-  }
-  return m.leaf_of_node[node];
 }
 
 // the packet at finest-unit position t in finest cell X: leaf, local cell,
@@ -268,36 +198,6 @@ __device__ bool mesh_cross(Packet<R>& p, const TransportArgs& a) {
   return false;
 }
 
-// A ray (direction om) in leaf `leaf` at local cell ci, fraction f whose
-// index on some axis left the leaf: the leaf beyond (leaf, lvl, ci, f
-// updated), or false if the ray left the domain.
-__device__ __forceinline__ bool mesh_ray_cross(const MeshDev& m, int& leaf, int& lvl, int ci[3], double f[3],
-                                               const double om[3]) {
-  const int4 o = reinterpret_cast<const int4*>(m.leaf_org)[leaf];
-  const double sz = (double)(1ll << (m.max_level - o.w));
-  const long long X0[3] = {o.x, o.y, o.z};
-  double t[3];
-  long long X[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    t[k] = (double)X0[k] + ((double)ci[k] + f[k]) * sz;
-    X[k] = finest_cell(t[k], om[k]);
-    if (X[k] < 0 || X[k] >= m.nfine[k]) return false;
-  }
-  leaf = mesh_find(m, X);
-  const int4 o1 = reinterpret_cast<const int4*>(m.leaf_org)[leaf];
-  lvl = o1.w;
-  const int sh = m.max_level - lvl;
-  const long long X1[3] = {o1.x, o1.y, o1.z};
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const long long i = (X[k] - X1[k]) >> sh;
-    ci[k] = (int)i;
-    f[k] = fmin(1.0, fmax(0.0, (t[k] - (double)X1[k]) / (double)(1ll << sh) - (double)i));
-  }
-  return true;
-}
-
 // flat index of the packet's cell
 template <bool MESH, typename R>
 __device__ __forceinline__ uint64_t cell_index(const Packet<R>& p, const TransportArgs& a) {
@@ -308,6 +208,17 @@ __device__ __forceinline__ uint64_t cell_index(const Packet<R>& p, const Transpo
   return (uint64_t)p.ci + (uint64_t)a.nx * ((uint64_t)p.cj + (uint64_t)a.ny * p.ck);
 }
 
+// Emission (Sec. 2.2).  Point sources: isotropic direction (or the pencil
+// direction), an unpolarised Stokes vector of weight lum/N, and the cell
+// holding the source (a coordinate on a face belongs to the cell the
+// direction points into).  Thermal emission of the dust (the alpha_abs B
+// term of eq. polarized-rt): the cell drawn by luminosity 4 pi rho kappa_abs
+// B V, the position uniform in it, an isotropic direction and the Stokes
+// vector w (alpha1, alpha2, 0, 0) in the grain-frame basis of the direction
+// (the dichroism of absorption is that of extinction), carried to the lab
+// basis; its mean over directions is w.  Draws: cell, three coordinates,
+// two for the direction.  Then an exponential scattering depth.  Returns
+// false if a point source lies outside the grid.
 template <typename R, bool ALIGNED, bool SPHERE, bool MESH>
 __device__ bool init_packet(Packet<R>& p, const ColdRef& k, uint64_t g, const TransportArgs& a) {
   int lo = 0, hi = a.n_lambda - 1;
@@ -478,27 +389,6 @@ __device__ __forceinline__ void coherency(const V3<R>& n, R Jp, R Jm, R JU, R JV
     out[NC > 8 ? 8 : 0] = v * n.z;
   }
 }
-
-// Components of the tally kept per cell and the per-cell stride in doubles:
-// spheres never create circular polarisation from unpolarised light, so the
-// antisymmetric (V) part of the coherency is identically zero.
-// Per-cell tally block of TS doubles (one 64- or 128-byte aligned block):
-// slots [0, NC) the coherency sums.  For non-spherical grains slot NC holds
-// the cell's density and slots NC+1..NC+4 the unit quaternion (w, x, y, z) of
-// its grain frame, formed once per run from the alignment direction (eq.
-// grain-quaternion) instead of at every step and scattering: the step that
-// enters a cell reads them from the block whose coherency it adds to when it
-// leaves, one 128-byte line instead of four (density and three direction
-// planes, 256 MB at 256^3, too large to stay in the Infinity Cache).  Spherical grains read the density from the compact FP32 array
-// (64 MB at 256^3), which stays cache-resident; there the density load is
-// the step's critical-path latency and the tally line's fetch is better
-// left to the atomics, off that path.
-template <bool SPHERE> struct TallyShape {
-  static constexpr int NC = SPHERE ? 6 : 9;
-  static constexpr int TS = SPHERE ? 8 : 16;
-  static constexpr int RHO = NC;
-  static constexpr bool HAS_B = !SPHERE;  // density and grain quaternion in slots NC..NC+4
-};
 
 // The grain-frame quaternion of a cell: from its tally block, or formed from
 // the alignment direction when the block does not hold it.
@@ -1070,40 +960,6 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
   return 0;
 }
 
-// ---------------------------------------------------------------------------
-// Shared by step 2 and peel-off: the Appendix A solution in its eigenbasis
-// and the Stokes source toward a camera formed from an incident coherency.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void appA_eigen(double a1, double a2, double a3, double dtau,
-                                           const double src[4], double s[4]) {
-  const double a = a1 + a2, b = a1 - a2;
-  const double A = s[0] + s[1], B = s[0] - s[1];
-  const double SA = src[0] + src[1], SB = src[0] - src[1];
-  const double An = A * exp(-a * dtau) + SA * dtau * phi1(a * dtau);
-  const double Bn = B * exp(-b * dtau) + SB * dtau * phi1(b * dtau);
-  double Un, Vn;
-  if (a3 == 0.0) {
-    const double e = exp(-a1 * dtau), g = dtau * phi1(a1 * dtau);
-    Un = s[2] * e + src[2] * g;
-    Vn = s[3] * e + src[3] * g;
-  } else {
-    // U + iV relaxes as exp(-(a1 - i a3) tau) toward the stationary state
-    const double x = -a1 * dtau, y = a3 * dtau;
-    const double ex = exp(x), cy = cos(y), sy = sin(y), sh = sin(0.5 * y);
-    const Cx<double> ez{ex * cy, ex * sy};
-    const Cx<double> em1{expm1(x) * cy - 2.0 * sh * sh, ex * sy};
-    const double den = x * x + y * y;
-    const Cx<double> phic{(em1.re * x + em1.im * y) / den, (em1.im * x - em1.re * y) / den};
-    const Cx<double> Z{s[2], s[3]}, SZ{src[2], src[3]};
-    const Cx<double> Zn = cadd(cmul(Z, ez), cscale(cmul(SZ, phic), dtau));
-    Un = Zn.re; Vn = Zn.im;
-  }
-  s[0] = 0.5 * (An + Bn);
-  s[1] = 0.5 * (An - Bn);
-  s[2] = Un;
-  s[3] = Vn;
-}
-
 // Stokes vector scattered toward a camera (basis e1 = theta_hat, e2 = phi_hat
 // of its direction) by a dipole whose incident coherency is C9 (real xx yy
 // zz xy xz yz, imaginary yz zx xy): rho'_ij = h_i^T C conj(h_j) with h_i =
@@ -1621,211 +1477,6 @@ k_transport64(TransportArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Step 2 (Sec. 2.3): one lane per (wavelength, view, pixel).  The ray enters
-// the grid box from the far side and is marched cell by cell toward the
-// camera; each cell applies the Appendix A solution with the cell's
-// extinction for the camera direction and the scattering source formed from
-// the coherency tally (or a caller-given per-view source).  FP64 throughout.
-// ---------------------------------------------------------------------------
-template <bool ALIGNED, bool SPHERE, bool USER_S, bool MESH>
-__global__ void __launch_bounds__(256) k_image(ImageArgs a) {
-  // No fused multiply-adds: a ray that grazes a cell face (a pixel centre on
-  // a face, drifting off it by ~1e-16 per cell) then takes the face-side
-  // decisions of a plain (unfused) evaluation of the same expressions.
-#pragma clang fp contract(off)
-  const uint64_t npix = (uint64_t)a.npx * a.npy;
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t total = npix * a.n_views * a.n_lambda;
-  if (idx >= total) return;
-  const int ix = (int)(idx % a.npx);
-  const int iy = (int)((idx / a.npx) % a.npy);
-  const int v = (int)((idx / npix) % a.n_views);
-  const int lam = (int)(idx / (npix * a.n_views));
-  const ViewDev vw = a.views[v];
-  const DustDev& D = a.dust[lam];
-  const double W = vw.half_width;
-  const double xp = -W + (ix + 0.5) * (2.0 * W / a.npx);
-  const double yp = -W + (iy + 0.5) * (2.0 * W / a.npy);
-  const double P0[3] = {xp * vw.px - yp * vw.tx, xp * vw.py - yp * vw.ty, xp * vw.pz - yp * vw.tz};
-  const double om[3] = {vw.ox, vw.oy, vw.oz};
-  const double lo[3] = {a.x0, a.y0, a.z0};
-  const int nn[3] = {a.nx, a.ny, a.nz};
-  double sn = -__builtin_huge_val(), sf = __builtin_huge_val();
-  bool miss = false;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if ((a.boundary >> k) & 1) continue;  // the periodic copies fill the axis
-    const double hi = lo[k] + nn[k] * a.dx;
-    if (om[k] != 0.0) {
-      const double s1 = (lo[k] - P0[k]) / om[k], s2 = (hi - P0[k]) / om[k];
-      sn = fmax(sn, fmin(s1, s2));
-      sf = fmin(sf, fmax(s1, s2));
-    } else if (P0[k] < lo[k] || P0[k] >= hi) {
-      miss = true;
-    }
-  }
-  double st[4] = {0.0, 0.0, 0.0, 0.0};
-  if (!miss && sn < sf) {
-    int ci[3];
-    double f[3];
-    // composite mesh: the leaf block of the ray, its level and origin
-    int leaf = 0, lvl = 0, sh = 0;
-    int4 org{0, 0, 0, 0};
-    const MeshDev& m = a.mesh;
-    const uint64_t B = MESH ? (uint64_t)m.block : 0;
-    if (MESH) {
-      // the entry point in finest cells, clamped into the domain
-      double t[3];
-      long long X[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        t[k] = (P0[k] + sn * om[k] - lo[k]) / m.fine;
-        X[k] = (long long)floor(t[k]);
-        X[k] = X[k] < 0 ? 0 : (X[k] > m.nfine[k] - 1 ? m.nfine[k] - 1 : X[k]);
-      }
-      leaf = mesh_find(m, X);
-      org = reinterpret_cast<const int4*>(m.leaf_org)[leaf];
-      lvl = org.w;
-      sh = m.max_level - lvl;
-      const long long X0[3] = {org.x, org.y, org.z};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const long long i = (X[k] - X0[k]) >> sh;
-        ci[k] = (int)i;
-        f[k] = fmin(1.0, fmax(0.0, (t[k] - (double)X0[k]) / (double)(1ll << sh) - (double)i));
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 3 && !MESH; ++k) {
-      const double t = (P0[k] + sn * om[k] - lo[k]) / a.dx;
-      const double fl = floor(t);
-      if ((a.boundary >> k) & 1) {
-        const long long n = nn[k], i = (long long)fl;
-        ci[k] = (int)(((i % n) + n) % n);
-        f[k] = fmin(1.0, fmax(0.0, t - fl));
-        continue;
-      }
-      int i = (int)fl;
-      i = i < 0 ? 0 : (i > nn[k] - 1 ? nn[k] - 1 : i);
-      ci[k] = i;
-      f[k] = fmin(1.0, fmax(0.0, t - (double)i));
-    }
-    const V3<double> Om{om[0], om[1], om[2]};
-    const V3<double> e1{vw.tx, vw.ty, vw.tz}, e2{vw.px, vw.py, vw.pz};
-    const double kext = D.kext;
-    double clen = MESH ? ldexp(a.dx, -lvl) : a.dx;
-    double inv_vol = 1.0 / (clen * clen * clen);
-    while (true) {
-      double tb = __builtin_huge_val();
-      int axis = -1;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double t;
-        if (om[k] > 0.0) t = (1.0 - f[k]) / om[k];
-        else if (om[k] < 0.0) t = -f[k] / om[k];
-        else continue;
-        if (t < tb) { tb = t; axis = k; }
-      }
-      if (axis < 0) break;
-      const uint64_t c = MESH ? (uint64_t)leaf * B * B * B + (uint64_t)ci[0] + B * ((uint64_t)ci[1] + B * ci[2])
-                              : (uint64_t)ci[0] + (uint64_t)a.nx * ((uint64_t)ci[1] + (uint64_t)a.ny * ci[2]);
-      const uint64_t sl = tally_slot(c, ci[0], ci[1], ci[2], MESH ? 0 : a.tbx, a.tby);
-      const double rho = (double)a.rho[c];
-      if (rho > 0.0) {
-        const double ke = rho * kext;
-        const double dtau = ke * tb * clen;
-        double S[4];
-        Quat<double> q{1.0, 0.0, 0.0, 0.0};
-        if (ALIGNED) q = grain_quat(V3<double>{(double)a.bx[c], (double)a.by[c], (double)a.bz[c]});
-        if (USER_S) {
-          const double* Sv = a.user_S + (((uint64_t)lam * a.nslot + sl) * a.n_views + v) * 4;
-          S[0] = Sv[0]; S[1] = Sv[1]; S[2] = Sv[2]; S[3] = Sv[3];
-        } else {
-          // source toward the camera from the incident coherency C of the
-          // cell: rho'_ij = h_i^T C conj(h_j), h_i = alpha e_i with the lab
-          // polarizability alpha = a_perp 1 + (a_par - a_perp) b b^T.
-          constexpr int TS = TallyShape<SPHERE>::TS;
-          const double* T = a.tally + ((uint64_t)lam * a.nslot + sl) * TS;
-          double C9[9] = {T[0], T[1], T[2], T[3], T[4], T[5], 0.0, 0.0, 0.0};
-          if (TallyShape<SPHERE>::NC == 9) { C9[6] = T[6]; C9[7] = T[7]; C9[8] = T[8]; }
-          source_toward<SPHERE>(C9, q, D, e1, e2, D.pfac * inv_vol, S);
-        }
-        const double ik = 1.0 / ke;
-        double src[4] = {S[0] * ik, S[1] * ik, S[2] * ik, S[3] * ik};
-        // the dust's thermal emission per unit optical depth,
-        // (kappa_abs / kappa_ext) (alpha1, alpha2, 0, 0) B in the grain-frame
-        // basis of the ray (eq. polarized-rt)
-        const double eB = a.em_B ? D.ka_cell / D.ke_cell * (double)a.em_B[(uint64_t)lam * a.ncell + c] : 0.0;
-        if (SPHERE && !ALIGNED) {
-          src[0] += eB;
-          const double E = exp(-dtau), G = dtau * phi1(dtau);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) st[k] = st[k] * E + src[k] * G;
-        } else {
-          V3<double> og = Om;
-          double c2 = 1.0, s2 = 0.0;
-          if (ALIGNED) {
-            og = to_grain(q, Om);
-            eta2(q, Om, og, c2, s2);
-          }
-          double a1, a2, a3;
-          alphas<double, SPHERE>(D, og.z, a1, a2, a3);
-          double sg[4] = {st[0], c2 * st[1] + s2 * st[2], -s2 * st[1] + c2 * st[2], st[3]};
-          const double srcg[4] = {src[0] + eB * a1, c2 * src[1] + s2 * src[2] + eB * a2,
-                                  -s2 * src[1] + c2 * src[2], src[3]};
-          appA_eigen(a1, a2, a3, dtau, srcg, sg);
-          st[0] = sg[0];
-          st[1] = c2 * sg[1] - s2 * sg[2];
-          st[2] = s2 * sg[1] + c2 * sg[2];
-          st[3] = sg[3];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        if (k != axis) f[k] = fmin(1.0, fmax(0.0, f[k] + tb * om[k]));
-      if (om[axis] > 0.0) { ci[axis]++; f[axis] = 0.0; } else { ci[axis]--; f[axis] = 1.0; }
-      if (MESH) {
-        if (ci[axis] >= 0 && ci[axis] < (int)B) continue;
-        // the leaf beyond the block face (finest-cell units, face rule)
-        const double sz = (double)(1ll << sh);
-        const long long X0[3] = {org.x, org.y, org.z};
-        double t[3];
-        long long X[3];
-        bool left = false;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          t[k] = (double)X0[k] + ((double)ci[k] + f[k]) * sz;
-          X[k] = finest_cell(t[k], om[k]);
-          left = left || X[k] < 0 || X[k] >= m.nfine[k];
-        }
-        if (left) break;
-        leaf = mesh_find(m, X);
-        org = reinterpret_cast<const int4*>(m.leaf_org)[leaf];
-        lvl = org.w;
-        sh = m.max_level - lvl;
-        const long long X1[3] = {org.x, org.y, org.z};
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const long long i = (X[k] - X1[k]) >> sh;
-          ci[k] = (int)i;
-          f[k] = fmin(1.0, fmax(0.0, (t[k] - (double)X1[k]) / (double)(1ll << sh) - (double)i));
-        }
-        clen = ldexp(a.dx, -lvl);
-        inv_vol = 1.0 / (clen * clen * clen);
-        continue;
-      }
-      if (ci[axis] < 0 || ci[axis] >= nn[axis]) {
-        if (!((a.boundary >> axis) & 1)) break;
-        ci[axis] = ci[axis] < 0 ? nn[axis] - 1 : 0;
-      }
-    }
-  }
-  double* out = a.images + (((uint64_t)lam * a.n_views + v) * 4) * npix + (uint64_t)iy * a.npx + ix;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) out[(uint64_t)k * npix] = st[k];
-}
-
-// ---------------------------------------------------------------------------
 // utility kernels
 // ---------------------------------------------------------------------------
 __global__ void k_fill_zero(uint64_t* p, uint64_t nwords, unsigned char* tail, int ntail) {
@@ -2081,26 +1732,6 @@ int transport_max_blocks_per_cu(bool fp64, bool aligned, bool sphere, bool peel,
   if (aligned) return occ_peel<true, false, false, false>(fp64, peel, block_size);
   if (sphere) return occ_peel<false, true, false, false>(fp64, peel, block_size);
   return occ_peel<false, false, false, false>(fp64, peel, block_size);
-}
-
-template <bool U, bool M>
-static void launch_image_one(const ImageArgs& a, bool aligned, bool sphere, dim3 grid, int bs, hipStream_t s) {
-  if (aligned && sphere) hipLaunchKernelGGL((k_image<true, true, U, M>), grid, dim3(bs), 0, s, a);
-  else if (aligned) hipLaunchKernelGGL((k_image<true, false, U, M>), grid, dim3(bs), 0, s, a);
-  else if (sphere) hipLaunchKernelGGL((k_image<false, true, U, M>), grid, dim3(bs), 0, s, a);
-  else hipLaunchKernelGGL((k_image<false, false, U, M>), grid, dim3(bs), 0, s, a);
-}
-
-hipError_t launch_image(const ImageArgs& a, bool aligned, bool sphere, bool user_source, bool mesh,
-                        hipStream_t s) {
-  const uint64_t total = (uint64_t)a.npx * a.npy * a.n_views * a.n_lambda;
-  const int bs = 128;
-  const dim3 grid((unsigned)((total + bs - 1) / bs));
-  if (user_source && mesh) launch_image_one<true, true>(a, aligned, sphere, grid, bs, s);
-  else if (user_source) launch_image_one<true, false>(a, aligned, sphere, grid, bs, s);
-  else if (mesh) launch_image_one<false, true>(a, aligned, sphere, grid, bs, s);
-  else launch_image_one<false, false>(a, aligned, sphere, grid, bs, s);
-  return hipGetLastError();
 }
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
