@@ -318,7 +318,7 @@ kp_status kp_run(kp_ctx *ctx, const uint64_t *packets_per_lambda, const kp_opts 
  * capture, tight serving loops, harnesses that forbid hipMalloc): kp_run
  * without any allocation.  Step 1 and step 2 run as in kp_run, with the
  * counters, the per-wavelength and camera tables and the step-1 tally held
- * in one static device array of the library (1 MiB + 256 MiB, one copy per
+ * in one static device array of the library (1 + 256 + 16 MiB, one copy per
  * device, held until the process ends) instead of context buffers; the
  * images go straight to d_images (device, borrowed, [n_lambda][n_views][4]
  * [npy][npx] FP64, n its element count).  Limits: the tally, n_lambda x

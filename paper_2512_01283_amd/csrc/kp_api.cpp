@@ -19,7 +19,8 @@ using namespace kp;
 
 // Device scratch of kp_run_static, the entry point that allocates nothing:
 // its counters and small tables (first KP_STATIC_HEAD bytes) and its step-1
-// tally (the next KP_STATIC_TALLY bytes).  Each device the library runs on
+// tally (the next KP_STATIC_TALLY bytes, with the copies of the cells around
+// a point source behind it).  Each device the library runs on
 // holds its own copy until the process ends.  In host code `scratch` names
 // a host-side stand-in: the device address of a device's copy comes from
 // hipGetSymbolAddress (scratch_address below) and only that address is ever
@@ -29,7 +30,7 @@ constexpr size_t KP_STATIC_HEAD = size_t(1) << 20;
 constexpr size_t KP_STATIC_TALLY = size_t(256) << 20;
 constexpr int KP_MAX_DEVICES = 64;
 }  // namespace
-static __device__ __align__(256) unsigned char scratch[KP_STATIC_HEAD + KP_STATIC_TALLY];
+static __device__ __align__(256) unsigned char scratch[KP_STATIC_HEAD + KP_STATIC_TALLY + HOT_BYTES];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -339,6 +340,12 @@ kp_status check_ready(kp_ctx* ctx) {
   return KP_OK;
 }
 
+bool all_spheres(const kp_ctx* ctx) {
+  for (const kp_dust& d : ctx->dust)
+    if (!is_sphere(d)) return false;
+  return true;
+}
+
 // Tally layout of the loaded grid: slots per wavelength and bricks along x
 // and y (tally_slot); a composite mesh keeps its cell order.
 struct TallyLayout {
@@ -349,6 +356,20 @@ TallyLayout tally_layout(const kp_ctx* ctx) {
   if (ctx->have_mesh) return TallyLayout{ctx->ncell, 0, 0};
   const kp_grid& g = ctx->grid;
   return TallyLayout{tally_slots(g.nx, g.ny, g.nz), (g.nx + 3) / 4, (g.ny + 3) / 4};
+}
+
+// Copies of the cells around the source that step 1 tallies into (HOT_SIDE):
+// for point sources and pencils on a uniform grid with coherency tallies, and
+// enough packets; what fits HOT_BYTES.  One copy would change nothing.
+int hot_copies(const kp_ctx* ctx, uint64_t total) {
+  if (ctx->src.kind == 2 || ctx->have_mesh || ctx->have_tables || total < HOT_MIN_PACKETS) return 0;
+  const size_t one = (size_t)HOT_CELLS * ctx->dust.size() * tally_stride(all_spheres(ctx)) * sizeof(double);
+  const size_t n = HOT_BYTES / one;
+  return n < 2 ? 0 : (n > (size_t)HOT_COPIES ? HOT_COPIES : (int)n);
+}
+// doubles of hot_copies(...) copies
+size_t hot_doubles(const kp_ctx* ctx, int copies) {
+  return (size_t)copies * HOT_CELLS * ctx->dust.size() * tally_stride(all_spheres(ctx));
 }
 
 // Step 2.  With user_source the source is the per-view array d_S (the
@@ -401,12 +422,6 @@ kp_status image_launch(kp_ctx* ctx, bool user_source, const double* d_S, double*
   KP_HIP(launch_image(a, aligned, sphere, user_source, ctx->have_mesh, s), "imaging kernel launch");
   KP_HIP(hipEventRecord(ctx->ev[3], s), "event record");
   return KP_OK;
-}
-
-bool all_spheres(const kp_ctx* ctx) {
-  for (const kp_dust& d : ctx->dust)
-    if (!is_sphere(d)) return false;
-  return true;
 }
 
 // The luminosity tables of the dust's thermal emission for every wavelength
@@ -485,6 +500,7 @@ struct RunBuffers {
   TraceDev* traces;              // [lambda][trace_packets] or null
   const ViewDev* views;          // camera table (uploaded by the caller)
   double* peel;                  // [lambda][view][4][npy][npx] peel-off images, or null
+  int hot_copies;                // copies of the cells around the source behind the tally
 };
 
 // Step 1 on prepared buffers: tally and counters cleared by kernels, the
@@ -506,6 +522,9 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
                              ctx->d_bhat ? ctx->d_bhat + 2 * ctx->ncell : nullptr, ctx->ncell, nl, all_sphere,
                              tl.nslot, ctx->grid.nx, ctx->grid.ny, tl.tbx, tl.tby, s),
            "tally initialisation");
+  if (b.hot_copies)
+    KP_HIP(launch_fill_zero(b.tally + (size_t)nl * tl.nslot * tally_stride(all_sphere),
+                            hot_doubles(ctx, b.hot_copies) * sizeof(double), s), "tally copies clear");
   KP_HIP(launch_fill_zero(b.stats, sizeof(StatsDev), s), "stats clear");
   KP_HIP(launch_fill_zero(b.counter, sizeof(unsigned long long), s), "counter clear");
   if (trace_need) KP_HIP(launch_fill_zero(b.traces, trace_need * sizeof(TraceDev), s), "trace clear");
@@ -536,6 +555,14 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   a.nslot = tl.nslot;
   a.tbx = tl.tbx;
   a.tby = tl.tby;
+  a.hot_copies = b.hot_copies;
+  a.hot_x = a.hot_y = a.hot_z = INT32_MIN;
+  if (b.hot_copies) {
+    const kp_grid& g = ctx->grid;
+    a.hot_x = (int)std::floor((ctx->src.pos[0] - g.x0) / g.dx) - HOT_SIDE / 2;
+    a.hot_y = (int)std::floor((ctx->src.pos[1] - g.y0) / g.dx) - HOT_SIDE / 2;
+    a.hot_z = (int)std::floor((ctx->src.pos[2] - g.z0) / g.dx) - HOT_SIDE / 2;
+  }
   a.counter = b.counter;
   a.stats = b.stats;
   a.traces = b.traces;
@@ -576,6 +603,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   KP_HIP(launch_transport(a, fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, (int)blocks, bs, s),
          "transport kernel launch");
   KP_HIP(hipEventRecord(ctx->ev[1], s), "event record");
+  if (b.hot_copies) KP_HIP(launch_hot_sum(a, sphere, s), "tally copies sum");
   KP_HIP(hipStreamSynchronize(s), "transport kernel");
 
   StatsDev h{};
@@ -951,13 +979,16 @@ kp_status kp_transport(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, vo
   const bool all_sphere = all_spheres(ctx);
   const int ts = tally_stride(all_sphere);
   const uint64_t nslot = tally_layout(ctx).nslot;
-  const size_t tally_need = ctx->have_tables ? (size_t)nl * nslot * ctx->views.size() * 4
-                                             : (size_t)nl * nslot * ts;
+  size_t tally_need = ctx->have_tables ? (size_t)nl * nslot * ctx->views.size() * 4
+                                       : (size_t)nl * nslot * ts;
+  int copies = hot_copies(ctx, total);
   const size_t trace_need = (size_t)nl * o->trace_packets;
   const size_t peel_need =
       o->peel_off ? (size_t)nl * ctx->views.size() * 4 * ctx->views[0].npx * ctx->views[0].npy : 0;
   size_t free_b = 0, total_b = 0;
   KP_HIP(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
+  if (copies && (tally_need + hot_doubles(ctx, copies)) * 8 > ctx->tally_n * 8 + free_b) copies = 0;
+  tally_need += hot_doubles(ctx, copies);
   size_t extra = (tally_need > ctx->tally_n ? tally_need * 8 : 0) +
                  (trace_need > ctx->traces_n ? trace_need * sizeof(TraceDev) : 0) +
                  (peel_need > ctx->peel_n ? peel_need * 8 : 0);
@@ -970,7 +1001,7 @@ kp_status kp_transport(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, vo
   fill_dust(ctx, counts, ctx->hdust);
   if ((st = upload_small(ctx, s))) return st;
   const RunBuffers buf{ctx->d_dust, ctx->d_tally, ctx->d_stats, ctx->d_counter, ctx->d_traces,
-                       ctx->d_views, o->peel_off ? ctx->d_peel : nullptr};
+                       ctx->d_views, o->peel_off ? ctx->d_peel : nullptr, copies};
   st = transport_launch(ctx, o, total, buf, s);
   if (st == KP_ERR_DEVICE || st == KP_ERR_OOM) return st;
   ctx->peel_valid_n = peel_need;
@@ -1071,7 +1102,7 @@ kp_status kp_run_static(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, d
   fill_dust(ctx, counts, ctx->hdust);
   KP_HIP(hipMemcpyAsync(d_dust, ctx->hdust.data(), dust_bytes, hipMemcpyHostToDevice, s), "dust upload");
   KP_HIP(hipMemcpyAsync(d_views, ctx->hviews.data(), view_bytes, hipMemcpyHostToDevice, s), "view upload");
-  const RunBuffers buf{d_dust, d_tally, d_stats, d_counter, nullptr, d_views, nullptr};
+  const RunBuffers buf{d_dust, d_tally, d_stats, d_counter, nullptr, d_views, nullptr, hot_copies(ctx, total)};
   st = transport_launch(ctx, o, total, buf, s);
   if (st == KP_ERR_DEVICE || st == KP_ERR_OOM) return st;
   kp_status st2 = ctx->have_tables

@@ -792,11 +792,12 @@ __device__ bool scatter_tab(Packet<R>& p, const ColdRef& k, const DustDev& D, ui
 // into the next cell (Russian roulette follows in the caller).  Returns 0 or
 // an end kind.
 template <typename R, bool ALIGNED, bool SPHERE, bool TAB, bool MESH>
-__device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a, bool& has, int64_t& key,
-                         R cc[TallyShape<SPHERE>::NC], bool& pending) {
+__device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a, uint64_t hot_base,
+                         bool& has, int64_t& key, R cc[TallyShape<SPHERE>::NC], bool& pending) {
   constexpr int NC = TallyShape<SPHERE>::NC;
   static_assert(!TAB || (SPHERE && !ALIGNED), "tabulated grains have scalar extinction");
   const uint64_t c = cell_index<MESH>(p, a);
+  const int ci0 = p.ci, cj0 = p.cj, ck0 = p.ck;
   p.last = (uint32_t)c;
   if (p.events >= a.max_events || p.steps >= KP_MAX_STEPS) {
     kc.hash() = hash_event(kc.hash(), END_BUDGET, c);
@@ -904,6 +905,12 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
         coherency<R, NC>(n, Jp, Jm, JU, JV, kb, cc);
       }
       key = (int64_t)((uint64_t)p.lam * a.nslot + sl);
+      if (!TAB && !MESH) {
+        // a cell of the box around the source: this wavefront's copy of it
+        const uint32_t hx = (uint32_t)(ci0 - a.hot_x), hy = (uint32_t)(cj0 - a.hot_y), hz = (uint32_t)(ck0 - a.hot_z);
+        if ((hx | hy | hz) < (uint32_t)HOT_SIDE)
+          key = (int64_t)(hot_base + (uint64_t)((uint32_t)p.lam * HOT_CELLS + (hx + HOT_SIDE * (hy + HOT_SIDE * hz))));
+      }
       has = true;
     }
   }
@@ -1325,6 +1332,10 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   int waited = 0;
   int64_t last_key = -1;  // key and staging slot of this lane's last entry (slot -1: drained)
   int slot = -1;
+  // first slot of this wavefront's copy of the cells around the source
+  const uint64_t hot_base =
+      a.hot_copies ? (uint64_t)a.n_lambda * (a.nslot + (uint64_t)HOT_CELLS * ((blockIdx.x * 4u + wv) % (uint32_t)a.hot_copies))
+                   : 0;
   unsigned long long flushes = 0;  // tally cells flushed by this wavefront
 
   // Packet ids reserved by this wavefront, [wnext, wend) (uniform).  With
@@ -1405,7 +1416,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     int64_t key = -1;
     R cc[NC];
     if (active && !pending) {
-      ended = step<R, ALIGNED, SPHERE, TAB, MESH>(p, kc, a, has, key, cc, pending);
+      ended = step<R, ALIGNED, SPHERE, TAB, MESH>(p, kc, a, hot_base, has, key, cc, pending);
       check = !ended && !pending;
     }
     if (TAB) {
@@ -1531,6 +1542,24 @@ __global__ void k_tally_init(double* tally, const float* rho, const float* bx, c
     }
     for (int lam = 0; lam < n_lambda; ++lam) tally[(uint64_t)lam * per + o] = v;
   }
+}
+
+// The cells of the box around the source: their copies added to the tally.  One
+// thread per (wavelength, cell, component); fixed order.
+__global__ void k_hot_sum(double* tally, uint64_t nslot, int n_lambda, int copies, int ts, int nc, int hx, int hy,
+                          int hz, int nx, int ny, int nz, int tbx, int tby) {
+  const int per = HOT_CELLS * nc;
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  const int lam = t / per, r = t - lam * per;
+  if (lam >= n_lambda) return;
+  const int w = r / nc, k = r - w * nc;
+  const int i = hx + (w % HOT_SIDE), j = hy + (w / HOT_SIDE) % HOT_SIDE, l = hz + w / (HOT_SIDE * HOT_SIDE);
+  if (i < 0 || j < 0 || l < 0 || i >= nx || j >= ny || l >= nz) return;
+  const double* h = tally + ((uint64_t)n_lambda * nslot + (uint64_t)lam * HOT_CELLS + w) * ts + k;
+  double s = 0.0;
+  for (int m = 0; m < copies; ++m) s += h[(uint64_t)m * n_lambda * HOT_CELLS * ts];
+  const uint64_t c = (uint64_t)i + (uint64_t)nx * ((uint64_t)j + (uint64_t)ny * (uint64_t)l);
+  if (s != 0.0) tally[((uint64_t)lam * nslot + tally_slot(c, i, j, l, tbx, tby)) * ts + k] += s;
 }
 
 __global__ void k_validate(const float* rho, const float* bx, const float* by, const float* bz,
@@ -1759,6 +1788,15 @@ hipError_t launch_tally_init(double* tally, const float* rho, const float* bx, c
   if (blocks == 0) blocks = 1;
   hipLaunchKernelGGL(k_tally_init, dim3((unsigned)blocks), dim3(256), 0, s, tally, rho, bx, by, bz, ncell,
                      n_lambda, lts, nc, co_b, nslot, nx, ny, tbx, tby);
+  return hipGetLastError();
+}
+
+hipError_t launch_hot_sum(const TransportArgs& a, bool sphere, hipStream_t s) {
+  const int nc = tally_components(sphere);
+  const int n = a.n_lambda * HOT_CELLS * nc;  // at most 1024 x 512 x 9
+  hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.tally, a.nslot, a.n_lambda,
+                     a.hot_copies, tally_stride(sphere), nc, a.hot_x, a.hot_y, a.hot_z, a.nx, a.ny, a.nz, a.tbx,
+                     a.tby);
   return hipGetLastError();
 }
 
