@@ -358,18 +358,23 @@ TallyLayout tally_layout(const kp_ctx* ctx) {
   return TallyLayout{tally_slots(g.nx, g.ny, g.nz), (g.nx + 3) / 4, (g.ny + 3) / 4};
 }
 
+// doubles a cell slot of the tally holds
+size_t cell_doubles(const kp_ctx* ctx) {
+  return ctx->have_tables ? 4 * ctx->views.size() : (size_t)tally_stride(all_spheres(ctx));
+}
+
 // Copies of the cells around the source that step 1 tallies into (HOT_SIDE):
-// for point sources and pencils on a uniform grid with coherency tallies, and
-// enough packets; what fits HOT_BYTES.  One copy would change nothing.
+// for point sources and pencils on a uniform grid, and enough packets; what
+// fits HOT_BYTES.  One copy would change nothing.
 int hot_copies(const kp_ctx* ctx, uint64_t total) {
-  if (ctx->src.kind == 2 || ctx->have_mesh || ctx->have_tables || total < HOT_MIN_PACKETS) return 0;
-  const size_t one = (size_t)HOT_CELLS * ctx->dust.size() * tally_stride(all_spheres(ctx)) * sizeof(double);
+  if (ctx->src.kind == 2 || ctx->have_mesh || total < HOT_MIN_PACKETS) return 0;
+  const size_t one = (size_t)HOT_CELLS * ctx->dust.size() * cell_doubles(ctx) * sizeof(double);
   const size_t n = HOT_BYTES / one;
   return n < 2 ? 0 : (n > (size_t)HOT_COPIES ? HOT_COPIES : (int)n);
 }
 // doubles of hot_copies(...) copies
 size_t hot_doubles(const kp_ctx* ctx, int copies) {
-  return (size_t)copies * HOT_CELLS * ctx->dust.size() * tally_stride(all_spheres(ctx));
+  return (size_t)copies * HOT_CELLS * ctx->dust.size() * cell_doubles(ctx);
 }
 
 // Step 2.  With user_source the source is the per-view array d_S (the
@@ -523,7 +528,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
                              tl.nslot, ctx->grid.nx, ctx->grid.ny, tl.tbx, tl.tby, s),
            "tally initialisation");
   if (b.hot_copies)
-    KP_HIP(launch_fill_zero(b.tally + (size_t)nl * tl.nslot * tally_stride(all_sphere),
+    KP_HIP(launch_fill_zero(b.tally + (size_t)nl * tl.nslot * cell_doubles(ctx),
                             hot_doubles(ctx, b.hot_copies) * sizeof(double), s), "tally copies clear");
   KP_HIP(launch_fill_zero(b.stats, sizeof(StatsDev), s), "stats clear");
   KP_HIP(launch_fill_zero(b.counter, sizeof(unsigned long long), s), "counter clear");
@@ -578,6 +583,11 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   a.mesh = mesh_dev(ctx);
   a.views = b.views;
   a.n_views = nv;
+  if (tab) {
+    a.tab_n = ctx->tab_nt;
+    const int64_t need = (6 * (int64_t)nl + 1) * ctx->tab_nt + 9 * (int64_t)nv;
+    a.tab_lds = need <= TAB_LDS_MAX ? (int)need : 0;
+  }
   if (b.peel) {
     a.npx = npx;
     a.npy = npy;
@@ -592,7 +602,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   const int bs = o->block_size ? o->block_size : 256;
   int bpc = o->blocks_per_cu;
   if (bpc == 0) {
-    bpc = transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, bs);
+    bpc = transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, bs, a.tab_lds);
     if (bpc < 1) bpc = 1;
     if (bpc > 8) bpc = 8;
   }
@@ -603,7 +613,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   KP_HIP(launch_transport(a, fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, (int)blocks, bs, s),
          "transport kernel launch");
   KP_HIP(hipEventRecord(ctx->ev[1], s), "event record");
-  if (b.hot_copies) KP_HIP(launch_hot_sum(a, sphere, s), "tally copies sum");
+  if (b.hot_copies) KP_HIP(launch_hot_sum(a, (int)cell_doubles(ctx), tab ? 4 * nv : tally_components(all_sphere), s), "tally copies sum");
   KP_HIP(hipStreamSynchronize(s), "transport kernel");
 
   StatsDev h{};
@@ -979,8 +989,7 @@ kp_status kp_transport(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, vo
   const bool all_sphere = all_spheres(ctx);
   const int ts = tally_stride(all_sphere);
   const uint64_t nslot = tally_layout(ctx).nslot;
-  size_t tally_need = ctx->have_tables ? (size_t)nl * nslot * ctx->views.size() * 4
-                                       : (size_t)nl * nslot * ts;
+  size_t tally_need = (size_t)nl * nslot * cell_doubles(ctx);
   int copies = hot_copies(ctx, total);
   const size_t trace_need = (size_t)nl * o->trace_packets;
   const size_t peel_need =

@@ -96,6 +96,11 @@ constexpr int HOT_COPIES = 32;                    // at most
 constexpr size_t HOT_BYTES = size_t(16) << 20;    // of all copies and wavelengths together
 constexpr uint64_t HOT_MIN_PACKETS = 1u << 15;    // fewer packets queue for less than the sum costs
 
+// LDS (doubles per block) that tabulated grains' tables may take with two
+// blocks of their kernel on a CU: one wavelength of 361 nodes and 16 cameras, or
+// two of 181
+constexpr int TAB_LDS_MAX = 3240;
+
 struct TransportArgs {
   const float* rho;
   const float* bx;
@@ -138,6 +143,9 @@ struct TransportArgs {
   // are added to (the kernels instantiated with peel-off)
   const ViewDev* views;
   int n_views, npx, npy;
+  // tabulated grains: nodes per table, and the doubles of LDS a block holds the
+  // tables and camera directions in (0: they are read from memory)
+  int tab_n, tab_lds;
   double* peel;
   MeshDev mesh;          // the kernels instantiated for a composite mesh
 };
@@ -203,9 +211,10 @@ hipError_t launch_tally_init(double* tally, const float* rho, const float* bx, c
 hipError_t launch_validate(const float* rho, const float* bx, const float* by, const float* bz,
                            uint64_t n, unsigned long long* bad, hipStream_t s);
 // adds the copies of the box around the source to the tally (hot_copies > 0)
-hipError_t launch_hot_sum(const TransportArgs& a, bool sphere, hipStream_t s);
+// (ts doubles per cell slot, the first nc of them sums)
+hipError_t launch_hot_sum(const TransportArgs& a, int ts, int nc, hipStream_t s);
 int transport_max_blocks_per_cu(bool fp64, bool aligned, bool sphere, bool peel, bool tab, bool mesh,
-                                int block_size);
+                                int block_size, int tab_lds);
 // Thermal emission tables of one wavelength: cdf [ncell], the running sum
 // of fac rho B (fac = 4 pi kappa_abs dx^3; on a composite mesh, leaf_org
 // non-null, times 2^-3 level of each cell's leaf, block3 cells per leaf) in

@@ -664,21 +664,38 @@ __device__ bool scatter(Packet<R>& p, const ColdRef& k, const Quat<R>& q, const 
 // over solid angle, at scattering angles uniform on [0, pi]; values are linear
 // in cos Theta between nodes.  FP64 throughout.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void tab_eval(const DustDev& D, double mu, double z[6]) {
-  const int n = D.tab_n;
+// The nodes come from the device arrays of a wavelength (the node interval by
+// the guide's entry for the cos Theta bin) or from a block's copy in LDS (by the
+// FP32 inverse cosine: no read on the dependency chain); either is then moved
+// to the interval holding mu.
+struct TabNodes {
+  const double* Z;       // [n][6]
+  const double* M;       // [n]
+  const int32_t* guide;  // [G] (device arrays)
+  int n, G;
+};
+__device__ __forceinline__ TabNodes tab_nodes(const DustDev& D) {
+  return TabNodes{D.tab, D.tab_mu, D.tab_guide, D.tab_n, D.tab_g};
+}
+template <bool LDS>
+__device__ __forceinline__ void tab_eval(const TabNodes& T, double mu, double z[6]) {
+  const int n = T.n;
   mu = fmin(1.0, fmax(-1.0, mu));
-  // the node interval: the guide's entry for the cos Theta bin (no inverse
-  // cosine on the dependency chain), then forward to the interval holding mu
-  const int G = D.tab_g;
-  int b = (int)((1.0 - mu) * (0.5 * (double)G));
-  b = b < 0 ? 0 : (b > G - 1 ? G - 1 : b);
-  int j = D.tab_guide[b];
-  const double* M = D.tab_mu;
+  int j;
+  if (LDS) {
+    j = (int)(acosf((float)mu) * ((float)(n - 1) * 0.31830988618f));
+    j = j < 0 ? 0 : (j > n - 2 ? n - 2 : j);
+  } else {
+    int b = (int)((1.0 - mu) * (0.5 * (double)T.G));
+    b = b < 0 ? 0 : (b > T.G - 1 ? T.G - 1 : b);
+    j = T.guide[b];
+  }
+  const double* M = T.M;
   while (j < n - 2 && mu < M[j + 1]) ++j;
   while (j > 0 && mu > M[j]) --j;
   const double ma = M[j], mb = M[j + 1];
   const double t = ma > mb ? (ma - mu) / (ma - mb) : 0.0;
-  const double* Z = D.tab + 6 * j;
+  const double* Z = T.Z + 6 * j;
 #pragma unroll
   for (int k = 0; k < 6; ++k) z[k] = (1.0 - t) * Z[k] + t * Z[6 + k];
 }
@@ -691,29 +708,41 @@ __device__ __forceinline__ void tab_eval(const DustDev& D, double mu, double z[6
 // rotation out of (e x m, e) into (tm, pm) is by -chi with
 // cos 2chi = ((n.tm)^2 - (n.pm)^2) / |n x m|^2, sin 2chi = 2 (n.tm)(n.pm) /
 // |n x m|^2: no square root or angle is formed.
-__device__ __forceinline__ void tab_toward(const DustDev& D, const V3<double>& n, const double s[4],
+template <bool LDS>
+__device__ __forceinline__ void tab_toward(const TabNodes& T, const V3<double>& n, const double s[4],
                                            const V3<double>& m, const V3<double>& tm,
                                            const V3<double>& pm, double out[4]) {
-  V3<double> thn, phn;
-  basis(n, thn, phn);
-  const double a = dot(m, thn), b = dot(m, phn);
-  const double w2 = a * a + b * b;
+  const double ct = dot(n, tm), cp = dot(n, pm);
+  const double w2 = ct * ct + cp * cp, r2 = n.x * n.x + n.y * n.y;
   double c2p = 1.0, s2p = 0.0, c2c, s2c;
-  if (w2 > 1e-24) {
-    const double iw = 1.0 / w2;
-    c2p = (a * a - b * b) * iw;
-    s2p = 2.0 * a * b * iw;
-    const double ct = dot(n, tm), cp = dot(n, pm);
+  if (w2 > 1e-24 && r2 > KP_POLE2) {
+    // a and b times sin theta of n, so that n's basis is not needed
+    const double a = n.z * (m.x * n.x + m.y * n.y) - r2 * m.z, b = m.y * n.x - m.x * n.y;
+    const double iq = 1.0 / (r2 * w2), iw = r2 * iq;
+    c2p = (a * a - b * b) * iq;
+    s2p = 2.0 * a * b * iq;
     c2c = (ct * ct - cp * cp) * iw;
     s2c = 2.0 * ct * cp * iw;
   } else {
-    const double cc = dot(phn, pm), ss = -dot(phn, tm);
-    c2c = cc * cc - ss * ss;
-    s2c = 2.0 * cc * ss;
+    V3<double> thn, phn;
+    basis(n, thn, phn);
+    const double a = dot(m, thn), b = dot(m, phn);
+    const double v2 = a * a + b * b;
+    if (v2 > 1e-24) {
+      const double iw = 1.0 / v2;
+      c2p = (a * a - b * b) * iw;
+      s2p = 2.0 * a * b * iw;
+      c2c = (ct * ct - cp * cp) * iw;
+      s2c = 2.0 * ct * cp * iw;
+    } else {
+      const double cc = dot(phn, pm), ss = -dot(phn, tm);
+      c2c = cc * cc - ss * ss;
+      s2c = 2.0 * cc * ss;
+    }
   }
   const double Qp = c2p * s[1] + s2p * s[2], Up = -s2p * s[1] + c2p * s[2];
   double z[6];
-  tab_eval(D, dot(n, m), z);
+  tab_eval<LDS>(T, dot(n, m), z);
   const double I = z[0] * s[0] + z[1] * Qp, Q = z[1] * s[0] + z[2] * Qp;
   const double U = z[3] * Up + z[4] * s[3], V = -z[4] * Up + z[5] * s[3];
   out[0] = I;
@@ -765,7 +794,7 @@ __device__ bool scatter_tab(Packet<R>& p, const ColdRef& k, const DustDev& D, ui
     V3<double> tm, pm;
     basis(m, tm, pm);
     double o[4];
-    tab_toward(D, n, s, m, tm, pm, o);
+    tab_toward<false>(tab_nodes(D), n, s, m, tm, pm, o);
     const double env = fmax(D.tab[6 * j], D.tab[6 * (j + 1)]) * (s[0] + plin);
     if (!(o[0] <= env * (1.0 + 1e-9))) return false;
     if (u4 * env <= o[0]) {
@@ -785,6 +814,9 @@ __device__ bool scatter_tab(Packet<R>& p, const ColdRef& k, const DustDev& D, ui
   return false;
 }
 
+constexpr int TAB_LVL_SHIFT = 47, TAB_LAM_SHIFT = 52;
+constexpr int TAB_CAP = 96;  // staged entries per wavefront (tabulated grains)
+
 // One loop iteration: one cell segment (Sec. 2.2: cell-to-cell traversal,
 // exponential scattering depth, continuous extinction across the segment by
 // the analytic cell solution of Appendix A, tally of the segment into the
@@ -797,7 +829,7 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
   constexpr int NC = TallyShape<SPHERE>::NC;
   static_assert(!TAB || (SPHERE && !ALIGNED), "tabulated grains have scalar extinction");
   const uint64_t c = cell_index<MESH>(p, a);
-  const int ci0 = p.ci, cj0 = p.cj, ck0 = p.ck;
+  const int ci0 = p.ci, cj0 = p.cj, ck0 = p.ck, lvl0 = MESH ? p.lvl : 0;
   p.last = (uint32_t)c;
   if (p.events >= a.max_events || p.steps >= KP_MAX_STEPS) {
     kc.hash() = hash_event(kc.hash(), END_BUDGET, c);
@@ -904,13 +936,15 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
       } else {
         coherency<R, NC>(n, Jp, Jm, JU, JV, kb, cc);
       }
-      key = (int64_t)((uint64_t)p.lam * a.nslot + sl);
-      if (!TAB && !MESH) {
+      uint64_t slot = (uint64_t)p.lam * a.nslot + sl;
+      if (!MESH) {
         // a cell of the box around the source: this wavefront's copy of it
         const uint32_t hx = (uint32_t)(ci0 - a.hot_x), hy = (uint32_t)(cj0 - a.hot_y), hz = (uint32_t)(ck0 - a.hot_z);
         if ((hx | hy | hz) < (uint32_t)HOT_SIDE)
-          key = (int64_t)(hot_base + (uint64_t)((uint32_t)p.lam * HOT_CELLS + (hx + HOT_SIDE * (hy + HOT_SIDE * hz))));
+          slot = hot_base + (uint64_t)((uint32_t)p.lam * HOT_CELLS + (hx + HOT_SIDE * (hy + HOT_SIDE * hz)));
       }
+      if (TAB) slot |= (uint64_t)p.lam << TAB_LAM_SHIFT | (MESH ? (uint64_t)lvl0 << TAB_LVL_SHIFT : 0ull);
+      key = (int64_t)slot;
       has = true;
     }
   }
@@ -1057,7 +1091,7 @@ __device__ void peel_off(const Packet<R>& p, const TransportArgs& a, const Quat<
     const V3<double> Om{vw.ox, vw.oy, vw.oz};
     double st[4];
     if (TAB)
-      tab_toward(D, V3<double>{p.nx, p.ny, p.nz}, s_in, Om, V3<double>{vw.tx, vw.ty, vw.tz},
+      tab_toward<false>(tab_nodes(D), V3<double>{p.nx, p.ny, p.nz}, s_in, Om, V3<double>{vw.tx, vw.ty, vw.tz},
                  V3<double>{vw.px, vw.py, vw.pz}, st);
     else
       source_toward<SPHERE>(C9, q_ev, D, V3<double>{vw.tx, vw.ty, vw.tz}, V3<double>{vw.px, vw.py, vw.pz},
@@ -1142,9 +1176,21 @@ __device__ void peel_off(const Packet<R>& p, const TransportArgs& a, const Quat<
 // by the L2's atomic line requests, and this cuts them four-fold.  Reached by
 // all lanes of the wavefront.  The source is per unit volume of the entry's
 // cell: on a composite mesh a cell of level l has (dx 2^-l)^3.
-template <bool MESH>
-__device__ void wave_drain_views(const TransportArgs& a, double* sv, long long* sk, double* sp, int lane,
-                                 int& staged) {
+//
+// A key holds the tally slot, and above it the cell's mesh level and the
+// wavelength.
+//
+// Where they fit (launch_transport) the tables of all wavelengths and the camera
+// directions are read from the block's LDS: the drain then makes no load from
+// memory, whose wait would also be for the atomics of the round before (gfx9
+// counts both in vmcnt).  128^3 disk, 181 nodes, 8 cameras, 2e6 packets: 34.1 ms
+// with the tables in memory, 21.8 in LDS (31.4 and 30.1 with one and two pairs per
+// lane and round from memory but without the 64-bit divisions and the square
+// root and quotient of n's basis); 9.5e7 entries x 4 lines at the L2's 2.35e10 atomics/s
+// are 16 ms.
+template <bool MESH, bool LDS>
+__device__ __forceinline__ void wave_drain_views(const TransportArgs& a, double* sv, long long* sk, double* sp,
+                                                 long long* sa, const double* tab, int lane, int& staged) {
   constexpr int NV = 7;  // staged values per entry: weighted J (4) and n (3)
   const int n = staged;
   if (n == 0) return;
@@ -1153,39 +1199,47 @@ __device__ void wave_drain_views(const TransportArgs& a, double* sv, long long* 
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const int nv = a.n_views;
-  const int items = n * nv;
+  const int items = n * nv;  // at most TAB_CAP x 4096
+  const float rnv = 1.0f / (float)nv;
   const double inv_vol = 1.0 / (a.dx * a.dx * a.dx);
+  const double* cams = tab + (6 * a.n_lambda + 1) * a.tab_n;
   for (int base = 0; base < items; base += 64) {
     const int it = base + lane;
-    double st[4] = {0.0, 0.0, 0.0, 0.0};
-    double iv = inv_vol;
     if (it < items) {
-      const int e = it / nv, v = it - e * nv;
+      int e = (int)((float)it * rnv), v = it - e * nv;
+      if (v < 0) { --e; v += nv; }
+      if (v >= nv) { ++e; v -= nv; }
       const double* x = sv + e * NV;
       const uint64_t key = (uint64_t)sk[e];
-      const DustDev& D = a.dust[key / a.nslot];
-      const ViewDev& vw = a.views[v];
+      const uint64_t slot = key & ((1ull << TAB_LVL_SHIFT) - 1ull);
+      const int lam = (int)(key >> TAB_LAM_SHIFT);
       const double s_in[4] = {x[0], x[1], x[2], x[3]};
-      tab_toward(D, V3<double>{x[4], x[5], x[6]}, s_in, V3<double>{vw.ox, vw.oy, vw.oz},
-                 V3<double>{vw.tx, vw.ty, vw.tz}, V3<double>{vw.px, vw.py, vw.pz}, st);
-      if (MESH) {
-        const uint64_t b = (uint64_t)a.mesh.block;
-        iv = ldexp(inv_vol, 3 * a.mesh.leaf_org[4 * ((key % a.nslot) / (b * b * b)) + 3]);
+      const V3<double> d{x[4], x[5], x[6]};
+      double st[4];
+      if (LDS) {
+        const double* c = cams + 9 * v;
+        const TabNodes T{tab + 6 * a.tab_n * lam, tab + 6 * a.tab_n * a.n_lambda, nullptr, a.tab_n, 0};
+        tab_toward<true>(T, d, s_in, V3<double>{c[0], c[1], c[2]}, V3<double>{c[3], c[4], c[5]},
+                         V3<double>{c[6], c[7], c[8]}, st);
+      } else {
+        const ViewDev& vw = a.views[v];
+        tab_toward<false>(tab_nodes(a.dust[lam]), d, s_in, V3<double>{vw.ox, vw.oy, vw.oz},
+                          V3<double>{vw.tx, vw.ty, vw.tz}, V3<double>{vw.px, vw.py, vw.pz}, st);
       }
-    }
+      const double iv = MESH ? ldexp(inv_vol, 3 * (int)((key >> TAB_LVL_SHIFT) & 31u)) : inv_vol;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sp[4 * lane + k] = st[k] * iv;
+      for (int k = 0; k < 4; ++k) sp[4 * lane + k] = st[k] * iv;
+      sa[lane] = (long long)((slot * (uint64_t)nv + (uint64_t)v) * 4);
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int d = 64 * j + lane;      // component d & 3 of pair d >> 2 of this round
-      const int pit = base + (d >> 2);
-      const double val = sp[d];
-      if (pit < items && val != 0.0) {
-        const int e = pit / nv, v = pit - e * nv;
-        unsafeAtomicAdd(a.tally + ((uint64_t)sk[e] * nv + v) * 4 + (d & 3), val);
+      if (base + (d >> 2) < items) {
+        const double val = sp[d];
+        if (val != 0.0) unsafeAtomicAdd(a.tally + sa[d >> 2] + (d & 3), val);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1309,13 +1363,25 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   // of aligned grains fit a CU; caps of 96 and 150 measured 1-3 % and 5 % slower on
   // the disk.
   constexpr int NSV = TAB ? 7 : NC;
-  constexpr int FLUSH_CAP = 128;
+  constexpr int FLUSH_CAP = TAB ? TAB_CAP : 128;
   static_assert(FLUSH_CAP > 64, "an area must take a wavefront's entries");
   __shared__ double s_val[4 * FLUSH_CAP * NSV];
   // tabulated grains: per wavefront the projections of one drain round
   __shared__ double s_proj[TAB ? 4 * 256 : 1];
+  __shared__ long long s_addr[TAB ? 4 * 64 : 1];
   __shared__ long long s_key[4 * FLUSH_CAP];
   __shared__ Cold s_cold[4];
+  // tabulated grains: the tables' nodes (contiguous on the device) and the
+  // camera directions (launch_transport)
+  extern __shared__ double s_tab[];
+  if (TAB && a.tab_lds) {
+    static_assert(!TAB || sizeof(s_val) + sizeof(s_proj) + sizeof(s_addr) + sizeof(s_key) + sizeof(s_cold) + 256 +
+                                  8 * TAB_LDS_MAX <= 80 * 1024, "two blocks per CU");
+    const int nt = (6 * a.n_lambda + 1) * a.tab_n;
+    for (int i = (int)threadIdx.x; i < nt; i += (int)blockDim.x) s_tab[i] = a.dust[0].tab[i];
+    for (int i = (int)threadIdx.x; i < 9 * a.n_views; i += (int)blockDim.x)
+      s_tab[nt + i] = (&a.views[i / 9].ox)[i % 9];
+  }
   if (threadIdx.x < SC_N) sc[threadIdx.x] = 0ull;
   if (threadIdx.x < SE_N) se[threadIdx.x] = 0.0;
   __syncthreads();
@@ -1324,6 +1390,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   const int wv = (int)(threadIdx.x >> 6);
   double* sv = s_val + wv * FLUSH_CAP * NSV;
   double* sp = s_proj + (TAB ? wv * 256 : 0);
+  long long* sa = s_addr + (TAB ? wv * 64 : 0);
   long long* sk = s_key + wv * FLUSH_CAP;
   const ColdRef kc{s_cold[wv], lane};
   int staged = 0;  // entries in this wavefront's staging area (uniform)
@@ -1424,7 +1491,10 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
       // segment's projection on the cameras depends on it)
       const double e7[7] = {(double)cc[0], (double)cc[1], (double)cc[2], (double)cc[3], p.nx, p.ny, p.nz};
       flushes += wave_stage_new<7>(has, key, e7, sv, sk, lane, staged, slot);
-      if (staged > FLUSH_CAP - 64) wave_drain_views<MESH>(a, sv, sk, sp, lane, staged);
+      if (staged > FLUSH_CAP - 64) {
+        if (a.tab_lds) wave_drain_views<MESH, true>(a, sv, sk, sp, sa, s_tab, lane, staged);
+        else wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
+      }
     } else {
       flushes += wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
       if (staged > FLUSH_CAP - 64) {
@@ -1452,7 +1522,8 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     if (check) ended = roulette<MESH>(p, kc, a);
     if (ended) active = false;
   }
-  if (TAB) wave_drain_views<MESH>(a, sv, sk, sp, lane, staged);
+  if (TAB && a.tab_lds) wave_drain_views<MESH, true>(a, sv, sk, sp, sa, s_tab, lane, staged);
+  else if (TAB) wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
   else wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
   if (lane == 0) atomicAdd(&sc[SC_FLUSH], flushes);
   __syncthreads();
@@ -1703,13 +1774,11 @@ hipError_t launch_emission_table(const float* rho, const float* B, double fac, c
 // ---------------------------------------------------------------------------
 template <bool A, bool S, bool T, bool M>
 static void launch_one(const TransportArgs& a, bool fp64, bool peel, int blocks, int bs, hipStream_t s) {
-  if (fp64 && peel) hipLaunchKernelGGL((k_transport64<A, S, true, T, M>), dim3(blocks), dim3(bs), 0, s, a);
-  else if (fp64) hipLaunchKernelGGL((k_transport64<A, S, false, T, M>), dim3(blocks), dim3(bs), 0, s, a);
-  else if (peel) hipLaunchKernelGGL((k_transport32<A, S, true, T, M>), dim3(blocks), dim3(bs), 0, s, a);
-  else hipLaunchKernelGGL((k_transport32<A, S, false, T, M>), dim3(blocks), dim3(bs), 0, s, a);
+  if (fp64 && peel) hipLaunchKernelGGL((k_transport64<A, S, true, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
+  else if (fp64) hipLaunchKernelGGL((k_transport64<A, S, false, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
+  else if (peel) hipLaunchKernelGGL((k_transport32<A, S, true, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
+  else hipLaunchKernelGGL((k_transport32<A, S, false, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
 }
-
-
 
 hipError_t launch_transport(const TransportArgs& a, bool fp64, bool aligned, bool sphere, bool peel, bool tab,
                             bool mesh, int blocks, int block_size, hipStream_t s) {
@@ -1735,28 +1804,29 @@ hipError_t launch_transport(const TransportArgs& a, bool fp64, bool aligned, boo
 }
 
 template <bool A, bool S, bool PL, bool T, bool M>
-static int occ_one(bool fp64, int bs) {
+static int occ_one(bool fp64, int bs, size_t lds) {
   int n = 0;
-  const hipError_t e = fp64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport64<A, S, PL, T, M>, bs, 0)
-                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport32<A, S, PL, T, M>, bs, 0);
+  const hipError_t e = fp64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport64<A, S, PL, T, M>, bs, lds)
+                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport32<A, S, PL, T, M>, bs, lds);
   return e == hipSuccess ? n : 0;
 }
 
 template <bool A, bool S, bool T, bool M>
-static int occ_peel(bool fp64, bool peel, int bs) {
-  return peel ? occ_one<A, S, true, T, M>(fp64, bs) : occ_one<A, S, false, T, M>(fp64, bs);
+static int occ_peel(bool fp64, bool peel, int bs, size_t lds = 0) {
+  return peel ? occ_one<A, S, true, T, M>(fp64, bs, lds) : occ_one<A, S, false, T, M>(fp64, bs, lds);
 }
 
 int transport_max_blocks_per_cu(bool fp64, bool aligned, bool sphere, bool peel, bool tab, bool mesh,
-                                int block_size) {
-  if (mesh && tab) return occ_peel<false, true, true, true>(fp64, peel, block_size);
+                                int block_size, int tab_lds) {
+  const size_t lds = (size_t)tab_lds * 8;
+  if (mesh && tab) return occ_peel<false, true, true, true>(fp64, peel, block_size, lds);
   if (mesh) {
     if (aligned && sphere) return occ_peel<true, true, false, true>(fp64, peel, block_size);
     if (aligned) return occ_peel<true, false, false, true>(fp64, peel, block_size);
     if (sphere) return occ_peel<false, true, false, true>(fp64, peel, block_size);
     return occ_peel<false, false, false, true>(fp64, peel, block_size);
   }
-  if (tab) return occ_peel<false, true, true, false>(fp64, peel, block_size);
+  if (tab) return occ_peel<false, true, true, false>(fp64, peel, block_size, lds);
   if (aligned && sphere) return occ_peel<true, true, false, false>(fp64, peel, block_size);
   if (aligned) return occ_peel<true, false, false, false>(fp64, peel, block_size);
   if (sphere) return occ_peel<false, true, false, false>(fp64, peel, block_size);
@@ -1791,12 +1861,10 @@ hipError_t launch_tally_init(double* tally, const float* rho, const float* bx, c
   return hipGetLastError();
 }
 
-hipError_t launch_hot_sum(const TransportArgs& a, bool sphere, hipStream_t s) {
-  const int nc = tally_components(sphere);
-  const int n = a.n_lambda * HOT_CELLS * nc;  // at most 1024 x 512 x 9
+hipError_t launch_hot_sum(const TransportArgs& a, int ts, int nc, hipStream_t s) {
+  const int n = a.n_lambda * HOT_CELLS * nc;  // below HOT_BYTES / 8
   hipLaunchKernelGGL(k_hot_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.tally, a.nslot, a.n_lambda,
-                     a.hot_copies, tally_stride(sphere), nc, a.hot_x, a.hot_y, a.hot_z, a.nx, a.ny, a.nz, a.tbx,
-                     a.tby);
+                     a.hot_copies, ts, nc, a.hot_x, a.hot_y, a.hot_z, a.nx, a.ny, a.nz, a.tbx, a.tby);
   return hipGetLastError();
 }
 
