@@ -607,7 +607,12 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
     if (bpc > 8) bpc = 8;
   }
   uint64_t blocks = (uint64_t)ctx->cu_count * bpc;
-  const uint64_t need_blocks = (total + bs - 1) / bs;
+  // packets per wavefront: all lanes, or, of a run that does not fill the chip, an
+  // equal share
+  const uint64_t waves = blocks * (uint64_t)(bs / 64), share = (total + waves - 1) / waves;
+  a.lanes = share < 64 ? (int)share : 64;
+  const uint64_t per_block = (uint64_t)a.lanes * (uint64_t)(bs / 64);
+  const uint64_t need_blocks = (total + per_block - 1) / per_block;
   if (blocks > need_blocks) blocks = need_blocks;
   KP_HIP(hipEventRecord(ctx->ev[0], s), "event record");
   KP_HIP(launch_transport(a, fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, (int)blocks, bs, s),

@@ -131,6 +131,7 @@ struct TransportArgs {
   uint32_t trace_count, trace_stride;
   int scatter_batch;  // run parked scattering events once this many lanes wait
   int scatter_wait;   // ... or after this many iterations
+  int lanes;          // packets a wavefront holds at most (1..64)
   // thermal emission of the dust (src_kind 2): per wavelength the running
   // sum of cell luminosities [lambda][ncell] and its guide table
   // [lambda][ncell + 1] (entry k: the first cell whose running sum exceeds

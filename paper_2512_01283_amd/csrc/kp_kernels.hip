@@ -1423,6 +1423,17 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   // a refill hands up to 64 idle lanes ids from one new chunk
   static_assert(WAVE_CHUNK >= 64, "a chunk must cover a whole wavefront");
   unsigned long long wnext = 0, wend = 0;
+  // A run of fewer packets than the chip has lanes gives each wavefront only
+  // `lanes` of them (launch_transport's caller): the time is then the longest
+  // packet's, whose every iteration also runs the paths that the wavefront's other
+  // packets take (4000 packets in a 32^3 sphere: 0.61 ms with full wavefronts, 0.43
+  // with two packets each; 2e4 in a refined sphere 1.41, 1.01).  The scattering batch
+  // is that share of its setting, and a share of what still moves at the end.
+  const int lanes = a.lanes;
+  const unsigned long long chunk = lanes < 64 ? (unsigned long long)lanes : WAVE_CHUNK;
+  // refill at this many packets or fewer: 0 once no ids are left (one threshold: a
+  // condition of two keeps 30 more registers alive)
+  int refill_at = lanes - max(1, REFILL_BATCH * lanes >> 6);
   bool global_done = false;  // the global counter has passed the total
   uint32_t ended = 0;        // this lane's packet has ended (its end kind), not yet reported
   while (true) {
@@ -1430,13 +1441,13 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     // REFILL_BATCH lanes of the wavefront at a time, or when no lane is left to
     // move: both run once for all of them instead of once per packet.
     const int nactive = __popcll(__ballot(active));
-    if (nactive == 0 || (!exhausted && 64 - nactive >= REFILL_BATCH)) {
+    if (nactive <= refill_at) {
       if (ended) {
         finish(p, kc, ended, reload_args(nactive), sc, se);
         ended = 0;
       }
       if (exhausted) break;  // nothing moves (nactive == 0) and no ids are left
-      const unsigned long long idle = __ballot(!active);
+      const unsigned long long idle = __ballot(!active && lane < lanes);
       const unsigned long long nidle = (unsigned long long)__popcll(idle);
       const int leader = __ffsll((unsigned long long)idle) - 1;
       bool have;
@@ -1447,18 +1458,18 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
         const bool refill = rem < nidle && !global_done;
         unsigned long long base = 0;
         if (refill) {
-          if (lane == leader) base = atomicAdd(a.counter, WAVE_CHUNK);
+          if (lane == leader) base = atomicAdd(a.counter, chunk);
           // the leader's value, as a wave-uniform (scalar) value
           const unsigned lo = __builtin_amdgcn_readlane((unsigned)base, leader);
           const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), leader);
           base = ((unsigned long long)hi << 32) | lo;
-          if (base + WAVE_CHUNK >= a.total) global_done = true;
+          if (base + chunk >= a.total) global_done = true;
         }
         have = r < rem || refill;
         g = r < rem ? wnext + r : base + (r - rem);
         if (refill) {
           wnext = base + (nidle - rem);
-          wend = base + WAVE_CHUNK;
+          wend = base + chunk;
         } else {
           wnext += nidle < rem ? nidle : rem;
         }
@@ -1471,7 +1482,8 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
         g = base + r;
         if (base + nidle >= a.total) exhausted = true;
       }
-      if (!active && have && g < a.total) {
+      if (exhausted) refill_at = 0;
+      if (!active && lane < lanes && have && g < a.total) {
         const bool in = init_packet<R, ALIGNED, SPHERE, MESH>(p, kc, g, reload_args(nactive));
         atomicAdd(&se[SE_EMIT], (double)p.I);  // the emitted intensity
         if (in) active = true;
@@ -1510,7 +1522,9 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     if (pm) {
       ++waited;
       const unsigned long long movable = __ballot(active && !ended && !pending);
-      if (__popcll(pm) >= a.scatter_batch || waited >= a.scatter_wait || movable == 0ull) {
+      // (with no packets left to take, a share of those still under way)
+      const int batch = exhausted ? a.scatter_batch * nactive >> 6 : a.scatter_batch * lanes >> 6;
+      if (__popcll(pm) >= batch || waited >= a.scatter_wait || movable == 0ull) {
         waited = 0;
         if (pending) {
           pending = false;
