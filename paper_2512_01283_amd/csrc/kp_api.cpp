@@ -522,7 +522,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   if (tab)
     KP_HIP(launch_fill_zero(b.tally, (size_t)nl * tl.nslot * nv * 4 * sizeof(double), s), "tally clear");
   else
-    KP_HIP(launch_tally_init(b.tally, ctx->d_rho, ctx->d_bhat,
+    KP_HIP(launch_tally_init(b.tally, ctx->d_bhat,
                              ctx->d_bhat ? ctx->d_bhat + ctx->ncell : nullptr,
                              ctx->d_bhat ? ctx->d_bhat + 2 * ctx->ncell : nullptr, ctx->ncell, nl, all_sphere,
                              tl.nslot, ctx->grid.nx, ctx->grid.ny, tl.tbx, tl.tby, s),

@@ -168,6 +168,56 @@ __device__ __forceinline__ void eta2(const Quat<R>& q, const V3<R>& n, const V3<
   s2 = (R)2 * c * s * ir;
 }
 
+// The grain axis b (the grain frame's z axis) of a quaternion.
+__device__ __forceinline__ V3<double> grain_axis(const Quat<double>& q) {
+  return {2.0 * (q.x * q.z + q.w * q.y), 2.0 * (q.y * q.z - q.w * q.x), 1.0 - 2.0 * (q.x * q.x + q.y * q.y)};
+}
+
+// cos 2eta, sin 2eta as eta2, from the axis alone: the grain frame's Q axis for
+// direction n is the projection of b on the plane across n, whose components
+// in n's basis, times sin theta of n, need no root.  Along the axis, where
+// dichroism vanishes, the angle is 0.
+__device__ __forceinline__ void eta2_axis(const V3<double>& b, const V3<double>& n, double& c2, double& s2) {
+  const double r2 = n.x * n.x + n.y * n.y;
+  double b1 = n.z * b.x, b2 = b.y;
+  if (r2 > KP_POLE2) {
+    b1 = n.z * (b.x * n.x + b.y * n.y) - r2 * b.z;
+    b2 = b.y * n.x - b.x * n.y;
+  }
+  const double q = b1 * b1 + b2 * b2;
+  c2 = 1.0;
+  s2 = 0.0;
+  if (q > KP_POLE2 * KP_POLE2) {
+    const double iq = 1.0 / q;
+    c2 = (b1 * b1 - b2 * b2) * iq;
+    s2 = 2.0 * b1 * b2 * iq;
+  }
+}
+
+// e^-x and phi1(x) = (1 - e^-x) / x from one evaluation: below 1/4 by phi1's
+// series (twelve terms, the first one left out is below 1e-17) and e^-x = 1 - x
+// phi1, else by e^-x and the quotient, which loses no digit there.
+__device__ __forceinline__ void exp_phi(double x, double& E, double& P) {
+  if (fabs(x) < 0.25) {
+    double s = 1.0 / 479001600.0;  // 1/12!
+    s = fma(-x, s, 1.0 / 39916800.0);
+    s = fma(-x, s, 1.0 / 3628800.0);
+    s = fma(-x, s, 1.0 / 362880.0);
+    s = fma(-x, s, 1.0 / 40320.0);
+    s = fma(-x, s, 1.0 / 5040.0);
+    s = fma(-x, s, 1.0 / 720.0);
+    s = fma(-x, s, 1.0 / 120.0);
+    s = fma(-x, s, 1.0 / 24.0);
+    s = fma(-x, s, 1.0 / 6.0);
+    s = fma(-x, s, 0.5);
+    P = fma(-x, s, 1.0);
+    E = fma(-x, P, 1.0);
+  } else {
+    E = exp(-x);
+    P = (1.0 - E) / x;
+  }
+}
+
 // 1 - e^{-x}  over x, i.e. (1 - e^{-x})/x with the x -> 0 limit
 template <typename R>
 __device__ __forceinline__ R phi1(R x) {

@@ -6,30 +6,6 @@ namespace kp {
 
 namespace {
 
-// e^-x and phi1(x) = (1 - e^-x) / x from one evaluation: below 1/4 by phi1's
-// series (twelve terms, the first one left out is below 1e-17) and e^-x = 1 - x
-// phi1, else by e^-x and the quotient, which loses no digit there.
-__device__ __forceinline__ void exp_phi(double x, double& E, double& P) {
-  if (fabs(x) < 0.25) {
-    double s = 1.0 / 479001600.0;  // 1/12!
-    s = fma(-x, s, 1.0 / 39916800.0);
-    s = fma(-x, s, 1.0 / 3628800.0);
-    s = fma(-x, s, 1.0 / 362880.0);
-    s = fma(-x, s, 1.0 / 40320.0);
-    s = fma(-x, s, 1.0 / 5040.0);
-    s = fma(-x, s, 1.0 / 720.0);
-    s = fma(-x, s, 1.0 / 120.0);
-    s = fma(-x, s, 1.0 / 24.0);
-    s = fma(-x, s, 1.0 / 6.0);
-    s = fma(-x, s, 0.5);
-    P = fma(-x, s, 1.0);
-    E = fma(-x, P, 1.0);
-  } else {
-    E = exp(-x);
-    P = (1.0 - E) / x;
-  }
-}
-
 // a . C b for a symmetric matrix C (xx yy zz xy xz yz) is m . C with
 // m = sym(a, b): the cell's six numbers against six constants of the camera
 struct Sym6 {
@@ -361,9 +337,8 @@ __global__ void __launch_bounds__(256) k_image(ImageArgs a) {
           double ib2 = 1.0;
           if (ALIGNED && a.axis_in_tally) {
             // the grain frame's z axis, from the block the coherency came from
-            const double* q = a.tally + ((uint64_t)lam * a.nslot + sl) * TallyShape<SPHERE>::TS + TallyShape<SPHERE>::RHO + 1;
-            const double qw = q[0], qx = q[1], qy = q[2], qz = q[3];
-            b = V3<double>{2.0 * (qx * qz + qw * qy), 2.0 * (qy * qz - qw * qx), 1.0 - 2.0 * (qx * qx + qy * qy)};
+            const double* q = a.tally + ((uint64_t)lam * a.nslot + sl) * TallyShape<SPHERE>::TS + TallyShape<SPHERE>::QUAT;
+            b = grain_axis(Quat<double>{q[0], q[1], q[2], q[3]});
           } else if (ALIGNED) {
             b = V3<double>{(double)a.bx[c], (double)a.by[c], (double)a.bz[c]};
             ib2 = 1.0 / dot(b, b);

@@ -194,9 +194,8 @@ inline uint64_t tally_slots(int nx, int ny, int nz) {
 
 // Tally layout [lambda][slot][stride] FP64: 6 reals (stride 8, one 64-B block
 // per cell) when every wavelength has spherical grains, else 9 (stride 16).
-// With stride 16 the slot after the coherency holds the cell's density and
-// the next four the unit quaternion of its grain frame (read by the
-// transport step from the same line its atomics update).
+// With stride 16 the four slots after the coherency hold the unit quaternion of
+// the cell's grain frame.
 inline int tally_components(bool sphere) { return sphere ? 6 : 9; }
 inline int tally_stride(bool sphere) { return sphere ? 8 : 16; }
 
@@ -206,7 +205,7 @@ hipError_t launch_transport(const TransportArgs& a, bool fp64, bool aligned, boo
 hipError_t launch_image(const ImageArgs& a, bool aligned, bool sphere, bool user_source, bool mesh,
                         hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_tally_init(double* tally, const float* rho, const float* bx, const float* by,
+hipError_t launch_tally_init(double* tally, const float* bx, const float* by,
                              const float* bz, uint64_t ncell, int n_lambda, bool sphere, uint64_t nslot, int nx,
                              int ny, int tbx, int tby, hipStream_t s);
 hipError_t launch_validate(const float* rho, const float* bx, const float* by, const float* bz,

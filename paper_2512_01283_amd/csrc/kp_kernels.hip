@@ -395,7 +395,7 @@ __device__ __forceinline__ void coherency(const V3<R>& n, R Jp, R Jm, R JU, R JV
 template <bool ALIGNED, bool SPHERE>
 __device__ __forceinline__ Quat<double> cell_quat(const TransportArgs& a, const double* blk, uint64_t c) {
   using TSh = TallyShape<SPHERE>;
-  if (TSh::HAS_B) return Quat<double>{blk[TSh::RHO + 1], blk[TSh::RHO + 2], blk[TSh::RHO + 3], blk[TSh::RHO + 4]};
+  if (TSh::HAS_B) return Quat<double>{blk[TSh::QUAT], blk[TSh::QUAT + 1], blk[TSh::QUAT + 2], blk[TSh::QUAT + 3]};
   return grain_quat(V3<double>{(double)a.bx[c], (double)a.by[c], (double)a.bz[c]});
 }
 
@@ -817,6 +817,13 @@ __device__ bool scatter_tab(Packet<R>& p, const ColdRef& k, const DustDev& D, ui
 constexpr int TAB_LVL_SHIFT = 47, TAB_LAM_SHIFT = 52;
 constexpr int TAB_CAP = 96;  // staged entries per wavefront (tabulated grains)
 
+// e^-x and (1 - e^-x) / x
+__device__ __forceinline__ void cell_exp(double x, double& E, double& P) { exp_phi(x, E, P); }
+__device__ __forceinline__ void cell_exp(float x, float& E, float& P) {
+  E = k_exp(-x);
+  P = phi1(x);
+}
+
 // One loop iteration: one cell segment (Sec. 2.2: cell-to-cell traversal,
 // exponential scattering depth, continuous extinction across the segment by
 // the analytic cell solution of Appendix A, tally of the segment into the
@@ -835,6 +842,12 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
     kc.hash() = hash_event(kc.hash(), END_BUDGET, c);
     return END_BUDGET;
   }
+  // the cell's grain frame, asked for before the geometry that does not need it
+  const double rhod = (double)p.rho;
+  const uint64_t sl = tally_slot(c, p.ci, p.cj, p.ck, MESH ? 0 : a.tbx, a.tby);
+  Quat<double> qd{1.0, 0.0, 0.0, 0.0};
+  if (ALIGNED && !SPHERE && rhod > 0.0)
+    qd = cell_quat<ALIGNED, SPHERE>(a, a.tally + ((uint64_t)p.lam * a.nslot + sl) * TallyShape<SPHERE>::TS, c);
   const double inf = __builtin_huge_val();
   const double dnx = p.nx, dny = p.ny, dnz = p.nz;
   // distances to the exit faces (reciprocals of n formed when n changes)
@@ -847,9 +860,6 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
   if (tz < td) { td = tz; axis = 2; }
   if (!(td < inf)) return END_NUMERIC;
   const DustDev& D = a.dust[p.lam];
-  const uint64_t sl = tally_slot(c, p.ci, p.cj, p.ck, MESH ? 0 : a.tbx, a.tby);
-  const double* blk = a.tally + ((uint64_t)p.lam * a.nslot + sl) * TallyShape<SPHERE>::TS;
-  const double rhod = TallyShape<SPHERE>::HAS_B ? blk[TallyShape<SPHERE>::RHO] : (double)p.rho;
   const double kbd = rhod * p.ks;
   double tld;
   bool scat;
@@ -857,12 +867,6 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
   else { tld = td; p.tau -= kbd * td; scat = false; }
   const R rho = (R)rhod, kb = (R)kbd, tl = (R)tld;
   p.steps++;
-  Quat<R> q{(R)1, (R)0, (R)0, (R)0};
-  Quat<double> qd{1.0, 0.0, 0.0, 0.0};
-  if (ALIGNED && rho > (R)0) {
-    qd = cell_quat<ALIGNED, SPHERE>(a, blk, c);
-    q = quat_cast<R>(qd);
-  }
   if (rho > (R)0 && tl > (R)0) {
     const V3<R> n{(R)p.nx, (R)p.ny, (R)p.nz};
     const R Ib = p.I;
@@ -882,12 +886,15 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
       // the grain-frame direction, the alphas and the exponents are formed in
       // FP64; the exponentials and the Stokes arithmetic run in R.
       const V3<double> nd{p.nx, p.ny, p.nz};
-      V3<double> ngd = nd;
-      if (ALIGNED) ngd = to_grain(qd, nd);
-      R c2 = (R)1, s2 = (R)0;
-      if (ALIGNED) eta2(q, n, V3<R>{(R)ngd.x, (R)ngd.y, (R)ngd.z}, c2, s2);
+      double ctd = nd.z, c2d = 1.0, s2d = 0.0;
+      if (ALIGNED) {
+        const V3<double> b = grain_axis(qd);
+        ctd = dot(b, nd);
+        eta2_axis(b, nd, c2d, s2d);
+      }
+      const R c2 = (R)c2d, s2 = (R)s2d;
       double a1, a2, a3;
-      alphas<double, SPHERE>(D, ngd.z, a1, a2, a3);
+      alphas<double, SPHERE>(D, ctd, a1, a2, a3);
       const double ked = rhod * p.ke;
       const double xAd = (ked * (a1 + a2) - kbd) * tld, xBd = (ked * (a1 - a2) - kbd) * tld;
       const double xUd = (ked * a1 - kbd) * tld, yd = ked * a3 * tld;
@@ -895,11 +902,16 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
       p.tau_path += (R)fabs(xUd);
       const R Qg = c2 * p.Q + s2 * p.U, Ug = -s2 * p.Q + c2 * p.U;
       const R A = p.I + Qg, B = p.I - Qg;
-      const R gA = tl * phi1(xA), gB = tl * phi1(xB);
-      const R eA = k_exp(-xA), eB = k_exp(-xB);
+      R gA, gB, eA, eB;
+      cell_exp(xA, eA, gA);
+      cell_exp(xB, eB, gB);
+      gA *= tl;
+      gB *= tl;
       R JUg, JVg, Un, Vn;
       if (yd == 0.0) {
-        const R gU = tl * phi1(xU), eU = k_exp(-xU);
+        R gU, eU;
+        cell_exp(xU, eU, gU);
+        gU *= tl;
         JUg = Ug * gU; JVg = p.V * gU;
         Un = Ug * eU; Vn = p.V * eU;
       } else {
@@ -996,7 +1008,7 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
       return END_ESCAPE;
     }
     // the next step's density, in flight while this iteration finishes
-    if (!TallyShape<SPHERE>::HAS_B) p.rho = a.rho[cell_index<MESH>(p, a)];
+    p.rho = a.rho[cell_index<MESH>(p, a)];
   }
   return 0;
 }
@@ -1583,19 +1595,19 @@ __global__ void k_fill_zero(uint64_t* p, uint64_t nwords, unsigned char* tail, i
 }
 
 // Tally blocks of non-spherical grains before a transport run: coherency slots
-// zero, the density in slot nc and the grain-frame quaternion of the alignment
-// direction (identity without one) in slots nc+1..nc+4, for every (wavelength,
-// cell) at its tally slot; the rest of each block, and the padding slots of the
-// bricks (never read), zero.  A wavefront takes 64 consecutive slots (a brick): each
-// lane forms one cell's five numbers, they meet in LDS, and the 64 blocks are
-// written for every wavelength in consecutive 16-byte stores.  Bound by the
+// zero and the grain-frame quaternion of the alignment direction (identity
+// without one) in the four slots after them, for every (wavelength, cell) at its
+// tally slot; the rest of each block, and the padding slots of the bricks (never
+// read), zero.  A wavefront takes 64 consecutive slots (a brick): each lane forms one
+// cell's quaternion, they meet in LDS, and the 64 blocks are written for every
+// wavelength in consecutive 16-byte stores.  Bound by the
 // writes: 2.1 GB (256^3) in 2.09 ms with one thread per double, five of sixteen
 // forming the quaternion, 0.52 ms so.
 constexpr int TI_NC = TallyShape<false>::NC, TI_TS = TallyShape<false>::TS;
-__global__ void __launch_bounds__(256) k_tally_init(double* tally, const float* rho, const float* bx, const float* by,
-                                                    const float* bz, uint64_t ncell, int n_lambda, uint64_t nslot,
+__global__ void __launch_bounds__(256) k_tally_init(double* tally, const float* bx, const float* by, const float* bz,
+                                                    uint64_t ncell, int n_lambda, uint64_t nslot,
                                                     int nx, int ny, int tbx, int tby) {
-  __shared__ double held[4][64 * 5];
+  __shared__ double held[4][64 * 4];
   const int lane = (int)(threadIdx.x & 63u);
   double* h = held[threadIdx.x >> 6];
   const uint64_t cxy = (uint64_t)nx * (uint64_t)ny;
@@ -1613,18 +1625,15 @@ __global__ void __launch_bounds__(256) k_tally_init(double* tally, const float* 
       valid = i < (uint64_t)nx && j < (uint64_t)ny && k < nz;
       c = i + (uint64_t)nx * j + cxy * k;
     }
-    double r = 0.0;
     Quat<double> q{0.0, 0.0, 0.0, 0.0};
     if (valid) {
-      r = (double)rho[c];
       q = Quat<double>{1.0, 0.0, 0.0, 0.0};
       if (bx) q = grain_quat(V3<double>{(double)bx[c], (double)by[c], (double)bz[c]});
     }
-    h[5 * lane] = r;
-    h[5 * lane + 1] = q.w;
-    h[5 * lane + 2] = q.x;
-    h[5 * lane + 3] = q.y;
-    h[5 * lane + 4] = q.z;
+    h[4 * lane] = q.w;
+    h[4 * lane + 1] = q.x;
+    h[4 * lane + 2] = q.y;
+    h[4 * lane + 3] = q.z;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1635,7 +1644,7 @@ __global__ void __launch_bounds__(256) k_tally_init(double* tally, const float* 
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int m = k + u - TI_NC;
-        v[u] = m >= 0 && m < 5 ? h[5 * cell + (m < 0 ? 0 : (m > 4 ? 4 : m))] : 0.0;
+        v[u] = m >= 0 && m < 4 ? h[4 * cell + (m < 0 ? 0 : (m > 3 ? 3 : m))] : 0.0;
       }
       if (g * 64 + (uint64_t)cell < nslot)
         for (int lam = 0; lam < n_lambda; ++lam)
@@ -1877,13 +1886,13 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_tally_init(double* tally, const float* rho, const float* bx, const float* by,
+hipError_t launch_tally_init(double* tally, const float* bx, const float* by,
                              const float* bz, uint64_t ncell, int n_lambda, bool sphere, uint64_t nslot, int nx,
                              int ny, int tbx, int tby, hipStream_t s) {
   if (sphere) return launch_fill_zero(tally, (size_t)n_lambda * nslot * tally_stride(true) * sizeof(double), s);
   uint64_t blocks = (nslot + 255) / 256;
   if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(k_tally_init, dim3((unsigned)blocks), dim3(256), 0, s, tally, rho, bx, by, bz, ncell, n_lambda,
+  hipLaunchKernelGGL(k_tally_init, dim3((unsigned)blocks), dim3(256), 0, s, tally, bx, by, bz, ncell, n_lambda,
                      nslot, nx, ny, tbx, tby);
   return hipGetLastError();
 }

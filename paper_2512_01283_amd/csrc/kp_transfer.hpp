@@ -100,21 +100,19 @@ __device__ __forceinline__ bool mesh_ray_cross(const MeshDev& m, int& leaf, int&
 // spheres never create circular polarisation from unpolarised light, so the
 // antisymmetric (V) part of the coherency is identically zero.
 // Per-cell tally block of TS doubles (one 64- or 128-byte aligned block):
-// slots [0, NC) the coherency sums.  For non-spherical grains slot NC holds
-// the cell's density and slots NC+1..NC+4 the unit quaternion (w, x, y, z) of
-// its grain frame, formed once per run from the alignment direction (eq.
-// grain-quaternion) instead of at every step and scattering: the step that
-// enters a cell reads them from the block whose coherency it adds to when it
-// leaves, one 128-byte line instead of four (density and three direction
-// planes, 256 MB at 256^3, too large to stay in the Infinity Cache).  Spherical grains read the density from the compact FP32 array
-// (64 MB at 256^3), which stays cache-resident; there the density load is
-// the step's critical-path latency and the tally line's fetch is better
-// left to the atomics, off that path.
+// slots [0, NC) the coherency sums.  For non-spherical grains slots NC..NC+3 hold
+// the unit quaternion (w, x, y, z) of the cell's grain frame, formed once per run
+// from the alignment direction (eq. grain-quaternion) instead of at every step and
+// scattering.  The density comes from the compact FP32 array (64 MB at 256^3, which
+// stays in the caches), asked for on entering the cell: an empty cell, half of a
+// disk's grid, then touches no block (aligned slab 18.1 -> 15.7 ms, batched disk
+// 27.6 -> 25.2, aligned 256^3 disk 12.6 -> 12.1 against the density in the block;
+// asking for the next cell's quaternion early too: 16.3, 26.4, 12.4).
 template <bool SPHERE> struct TallyShape {
   static constexpr int NC = SPHERE ? 6 : 9;
   static constexpr int TS = SPHERE ? 8 : 16;
-  static constexpr int RHO = NC;
-  static constexpr bool HAS_B = !SPHERE;  // density and grain quaternion in slots NC..NC+4
+  static constexpr int QUAT = NC;
+  static constexpr bool HAS_B = !SPHERE;  // grain quaternion in slots NC..NC+3
 };
 
 // ---------------------------------------------------------------------------
