@@ -10,289 +10,22 @@
 // buffer.  Pixel p = (n H + h) W + w.  Every channel count is a multiple of 8,
 // so 8 consecutive channels are one 16-byte load.
 //
-// Convolutions are implicit GEMMs on v_mfma_f32_16x16x32_bf16 (FP32
-// accumulation).  The GEMM K index is k = kk * cin + c with kk = 3 dy + dx
+// Convolutions (kp_conv.hip) are implicit GEMMs on v_mfma_f32_16x16x32_bf16
+// (FP32 accumulation).  The GEMM K index is k = kk * cin + c with kk = 3 dy + dx
 // the tap and c the input channel; K = 9 cin is zero-padded to a multiple of
 // 32 in the packed weights.  A lane's 8 consecutive K elements never straddle
 // a tap because cin % 8 == 0.
-//
-// MFMA 16x16x32 BF16 operand layout (wave64, lane l, i = l % 16, g = l / 16):
-// A[i][8g + j] and B[8g + j][i] for j = 0..7 come from lane l; the result
-// D[4g + j][i], j = 0..3, lands in lane l.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 #include <cmath>
 
+#include "kp_dn_device.hpp"
 #include "kp_dn_internal.hpp"
 
 namespace kp {
 namespace dn {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even (inputs are finite)
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-__device__ __forceinline__ bool bf_pos(uint16_t b) { return !(b & 0x8000u) && b != 0; }
-
-__device__ __forceinline__ u32x4 ld16(const uint16_t* p) { return *(const u32x4*)p; }
-__device__ __forceinline__ void st16(uint16_t* p, u32x4 v) { *(u32x4*)p = v; }
-
-// unpack / pack 8 BF16 held in a 16-byte vector
-__device__ __forceinline__ void unpack8(u32x4 v, float* f) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    f[2 * j] = __uint_as_float(v[j] << 16);
-    f[2 * j + 1] = __uint_as_float(v[j] & 0xFFFF0000u);
-  }
-}
-__device__ __forceinline__ u32x4 pack8(const float* f) {
-  u32x4 v;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] = (uint32_t)f2bf(f[2 * j]) | ((uint32_t)f2bf(f[2 * j + 1]) << 16);
-  return v;
-}
-
-__device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                 0, 0, 0);
-}
-
-// ---------------------------------------------------------------------------
-// 3x3 convolution as an implicit GEMM:
-//   y[p][n] = epi( sum_{kk, c} x[p + off(kk)][c] * w[n][kk * cin + c] )
-// off(kk) = (kk / 3 - 1, kk % 3 - 1), zero outside the image.  The forward
-// pass uses the layer's weights; the input gradient of a layer uses the same
-// kernel with the flipped, transposed weights wd[ci][kk * cout + co] =
-// w[co][8 - kk][ci], because off(8 - kk) = -off(kk).
-// One wave computes 32 pixels x 64 output channels (2 x 4 MFMA tiles).
-// ---------------------------------------------------------------------------
-// MODE: CONV_RELU (bias, relu), CONV_LINEAR (bias), CONV_MASK (no bias; zero where mask <= 0 if mask)
-template <int MODE>
-__global__ void __launch_bounds__(256) k_conv3(ConvArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int P = a.B * a.H * a.W;
-  const int ngroups = (a.nout + 63) >> 6;
-  const int ptile = wave / ngroups, ng = wave - ptile * ngroups;
-  if (ptile * 32 >= P) return;
-  const int i = lane & 15, g = lane >> 4;
-  int ph[2], pw[2], pn[2];
-  bool pv[2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int p = ptile * 32 + 16 * r + i;
-    pv[r] = p < P;
-    const int q = pv[r] ? p : 0;
-    pw[r] = q % a.W;
-    ph[r] = (q / a.W) % a.H;
-    pn[r] = q / (a.W * a.H);
-  }
-  const int n0 = ng * 64;
-  const int ntile = min(4, (a.nout - n0) >> 4);
-  f32x4 acc[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* wrow[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) wrow[t] = a.w + (size_t)(n0 + 16 * min(t, ntile - 1) + i) * a.kp + 8 * g;
-  const int K = 9 * a.cin;
-  int kk = 0, c = 8 * g;
-  while (c >= a.cin) {
-    c -= a.cin;
-    ++kk;
-  }
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    const int dy = kk / 3 - 1, dx = kk % 3 - 1;
-    u32x4 av[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int hh = ph[r] + dy, ww = pw[r] + dx;
-      const bool ok = pv[r] && kk < 9 && hh >= 0 && hh < a.H && ww >= 0 && ww < a.W;
-      av[r] = ok ? ld16(a.x + ((size_t)(pn[r] * a.H + hh) * a.W + ww) * a.xs + c) : zero;
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < ntile) {
-        const u32x4 bv = ld16(wrow[t] + k0);
-        acc[0][t] = mfma(av[0], bv, acc[0][t]);
-        acc[1][t] = mfma(av[1], bv, acc[1][t]);
-      }
-    }
-    c += 32;
-    while (c >= a.cin) {
-      c -= a.cin;
-      ++kk;
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    if (t >= ntile) continue;
-    const int n = n0 + 16 * t + i;
-    const float bn = MODE == CONV_MASK ? 0.f : a.bias[n];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int p = ptile * 32 + 16 * r + 4 * g + j;
-        if (p >= P) continue;
-        float v = acc[r][t][j] + bn;
-        if (MODE == CONV_RELU) v = fmaxf(v, 0.f);
-        if (MODE == CONV_MASK && a.mask && !bf_pos(a.mask[(size_t)p * a.ms + n])) v = 0.f;
-        a.y[(size_t)p * a.ys + n] = f2bf(v);
-      }
-  }
-}
-
-// LDS access rule of gfx950 used by the layouts below (measured with the
-// SQ_LDS_BANK_CONFLICT counter on access patterns of known shape): 64 banks
-// of 4 bytes; a 16-byte access is served in four passes of 16 lanes, the
-// pass of lane L being (bit 5 of L, parity of bits 2, 3 and 4 of L); an
-// 8-byte access in two passes of 32 consecutive lanes.  A pass without two
-// lanes on one bank (at different addresses) takes one cycle.
-//
-// The same convolution with the input tile staged in LDS: a workgroup owns a
-// 16 x 16 block of output pixels of one image x 16 NT output channels; each
-// wave computes 4 rows of it (64 pixels) x 16 NT channels (4 x NT MFMA tiles).
-// NT (1..4) divides cout / 16, so no tile is partial and no MFMA is wasted.  The K
-// loop runs over blocks of 32 input channels: per block the 18 x 18 input
-// halo (zero outside the image and past cin) and the weights of all 9 taps
-// for these channels go to LDS once, and the 9 taps then read their operands
-// from it, so each input value is fetched from memory once instead of once
-// per tap.  LDS rows (a pixel's or an output channel's 32 channels) are
-// padded to 80 bytes and a row's four 16-byte chunks stored in the order
-// 0, 2, 1, 3; MFMA row i of an operand tile is pixel (or channel) ch_row(i)
-// of the 16, a permutation found by exhaustive search under the rule above
-// for which every 16-byte operand read is conflict-free at any row offset;
-// every operand address is a per-lane base plus an immediate.  The
-// next block's loads are in flight in registers during the current block's
-// 144 MFMAs per wave.
-constexpr int CH_E = 18;                  // halo edge (16 + 2)
-constexpr int CH_ROWB = 80;               // LDS bytes per row: 64 data + 16 pad
-constexpr int CH_HALO_B = CH_E * CH_E * CH_ROWB;
-constexpr int CH_LDS_B = CH_HALO_B + 9 * 64 * CH_ROWB;
-constexpr int CH_NH = (CH_E * CH_E * 4 + 255) / 256;  // halo chunks per thread (6)
-
-// LDS slot of 16-byte chunk c of a row, and the tile row held by MFMA row i
-__device__ __forceinline__ int ch_slot(int c) { return ((c & 1) << 1) | (c >> 1); }
-// ch_row: 0 2 4 6 1 3 5 7 9 11 13 15 8 10 12 14
-__device__ __forceinline__ int ch_row(int i) { return (((i & 3) << 1) | ((i >> 2) & 1) | (i & 8)) ^ (i >> 3); }
-
-template <int MODE, int NT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_conv3_halo(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[CH_LDS_B];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const int ngroups = a.nout / (16 * NT);
-  const int txn = (a.W + 15) >> 4, tyn = (a.H + 15) >> 4;
-  int bid = blockIdx.x;
-  const int ng = bid % ngroups;
-  bid /= ngroups;
-  const int tx = bid % txn;
-  bid /= txn;
-  const int ty = bid % tyn;
-  const int img = bid / tyn;
-  const int n0 = ng * 16 * NT;
-  const int y0 = ty * 16, x0 = tx * 16;
-  // loader slots: 16-byte chunk c = tid & 3 (channels 8c..8c+7 of the block)
-  // of halo pixels (tid >> 2) + 64 u and of weight rows (tap u, channel tid >> 2)
-  const int c8 = (tid & 3) * 8;
-  int hpix[CH_NH];  // input pixel of each halo slot, -1 outside the image or the halo
-#pragma unroll
-  for (int u = 0; u < CH_NH; ++u) {
-    const int hp = (tid >> 2) + 64 * u;
-    const int hy = hp / CH_E, hx = hp - hy * CH_E;
-    const int yy = y0 + hy - 1, xx = x0 + hx - 1;
-    const bool ok = hp < CH_E * CH_E && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W;
-    hpix[u] = ok ? (img * a.H + yy) * a.W + xx : -1;
-  }
-  const int hdst = (tid >> 2) * CH_ROWB + ch_slot(tid & 3) * 16;  // + 64 u rows
-  const int wco = tid >> 2;
-  const uint16_t* wsrc = wco < 16 * NT ? a.w + (size_t)(n0 + wco) * a.kp + c8 : nullptr;
-  const int wdst = CH_HALO_B + wco * CH_ROWB + ch_slot(tid & 3) * 16;  // + 64 u rows
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  u32x4 hv[CH_NH], wvv[9];
-  auto load = [&](int cb) {
-    const int ch = cb * 32 + c8;
-    const bool cok = ch < a.cin;
-#pragma unroll
-    for (int u = 0; u < CH_NH; ++u)
-      hv[u] = (cok && hpix[u] >= 0) ? ld16(a.x + (size_t)hpix[u] * a.xs + ch) : zero;
-#pragma unroll
-    for (int u = 0; u < 9; ++u) wvv[u] = (cok && wsrc) ? ld16(wsrc + u * a.cin + cb * 32) : zero;
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int u = 0; u < CH_NH; ++u)
-      if ((tid >> 2) + 64 * u < CH_E * CH_E) *(u32x4*)(lds + hdst + u * 64 * CH_ROWB) = hv[u];
-    if (wsrc)
-#pragma unroll
-      for (int u = 0; u < 9; ++u) *(u32x4*)(lds + wdst + u * 64 * CH_ROWB) = wvv[u];
-  };
-  f32x4 acc[4][NT];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // operand bases: MFMA row i reads tile pixel (4 wv, ch_row(i)) at halo pixel
-  // (4 wv + 1, ch_row(i) + 1) (the taps add -1..1) and output channel ch_row(i)
-  const unsigned char* abase = lds + (4 * wv * CH_E + ch_row(i)) * CH_ROWB + 16 * ch_slot(g);
-  const unsigned char* bbase = lds + CH_HALO_B + ch_row(i) * CH_ROWB + 16 * ch_slot(g);
-  const int nb = (a.cin + 31) >> 5;
-  load(0);
-  for (int cb = 0; cb < nb; ++cb) {
-    if (cb > 0) __syncthreads();
-    store();
-    __syncthreads();
-    if (cb + 1 < nb) load(cb + 1);
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int dy = tap / 3, dx = tap % 3;  // halo offsets 0..2
-      u32x4 av[4], bv[NT];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) av[r] = *(const u32x4*)(abase + ((r + dy) * CH_E + dx) * CH_ROWB);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) bv[t] = *(const u32x4*)(bbase + (tap * 64 + 16 * t) * CH_ROWB);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r][t] = mfma(av[r], bv[t], acc[r][t]);
-      // keep the scheduler from hoisting later taps' operand reads (registers)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int n = n0 + 16 * t + ch_row(i);
-    const float bn_v = MODE == CONV_MASK ? 0.f : a.bias[n];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int yy = y0 + 4 * wv + r;
-      if (yy >= a.H) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int xx = x0 + ch_row(4 * g + j);
-        if (xx >= a.W) continue;
-        const size_t p = (size_t)(img * a.H + yy) * a.W + xx;
-        float v = acc[r][t][j] + bn_v;
-        if (MODE == CONV_RELU) v = fmaxf(v, 0.f);
-        if (MODE == CONV_MASK && a.mask && !bf_pos(a.mask[p * a.ms + n])) v = 0.f;
-        a.y[p * a.ys + n] = f2bf(v);
-      }
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Weight gradient:  gw[co][kk][c] += sum_p gz[p][co] * x[p + off(kk)][c]
@@ -307,7 +40,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 // are a channel's 128 pixels; the 16-byte chunk c of row r sits at chunk
 // position c ^ 2 ((r ^ (r >> 3)) & 7), which keeps both the transposing
 // 8-byte stores and the MFMA operand reads (8 consecutive pixels, one 16-byte
-// read) free of bank conflicts under the LDS access rule stated below.  Each wave runs 16 MFMAs per slab; the next slab's global
+// read) free of bank conflicts under the LDS access rule of kp_dn_device.hpp.  Each wave runs 16 MFMAs per slab; the next slab's global
 // loads are in flight meanwhile (double-buffered LDS, one barrier per slab).
 // Partial tiles are added to the FP32 gradient with atomics; the workgroups
 // of the first K tile also add the bias gradient sum_p gz[p][co].  About 1024
@@ -533,7 +266,6 @@ constexpr int WH_CHB = WH_HR * WH_ROWB + 32;  // LDS bytes per channel (672)
 constexpr int WH_GZB = 64 * 128 * 2;          // gz^T: 64 channels x 128 pixels
 constexpr int WH_BUF = WH_GZB + 64 * WH_CHB;  // one tile's operands (59392 bytes)
 constexpr int WH_TARGET = 256;                // workgroups per launch (one per CU)
-constexpr int WH_MIN_CIN = 48;                // narrower inputs keep k_wgrad
 
 __global__ void __launch_bounds__(512) k_wgrad_halo(WgradArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * WH_BUF];
@@ -559,6 +291,9 @@ __global__ void __launch_bounds__(512) k_wgrad_halo(WgradArgs a) {
   const int lt = tid & 255;
   const int sp = lt >> 3, a8 = lt & 7, s8 = 8 * a8;
   const bool a_ok = m0 + s8 < a.cout, x_ok = c0 + s8 < a.cin;
+  const bool low = a.xl && c0 + s8 < a.cl;  // this lane's channels come from the half-resolution map
+  const uint16_t* xsrc = (low ? a.xl : a.x) + c0 + s8;
+  const int xstr = low ? a.xls : a.xs;
   const int u0 = lt >> 3;
   const bool u1_ok = u0 + 32 < WH_NU;
   int xst[2];  // byte offset of channel s8's row slot for each quad; + j * WH_CHB per channel
@@ -601,12 +336,12 @@ __global__ void __launch_bounds__(512) k_wgrad_halo(WgradArgs a) {
         const int u = u0 + 32 * v, hr = u % WH_HR, q = u / WH_HR;
         const int yy = y0 + hr - 1, xb = x0 + 4 * q - 1;
         const bool rok = x_ok && (v == 0 || u1_ok) && yy >= 0 && yy < a.H;
-        const size_t prow = (size_t)(img * a.H + yy) * a.W;
+        const size_t prow = low ? (size_t)(img * (a.H >> 1) + (yy >> 1)) * (a.W >> 1) : (size_t)(img * a.H + yy) * a.W;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int xx = xb + e;
           const bool ok = rok && 4 * q + e < WH_TW + 2 && xx >= 0 && xx < a.W;
-          pre[4 * v + e] = ok ? ld16(a.x + (prow + xx) * a.xs + c0 + s8) : zero;
+          pre[4 * v + e] = ok ? ld16(xsrc + (prow + (xx >> (int)low)) * xstr) : zero;
         }
       }
     }
@@ -1158,32 +893,6 @@ static inline unsigned grid_for(size_t n, size_t cap = 65536) {
   size_t g = (n + 255) / 256;
   if (g > cap) g = cap;
   return (unsigned)(g ? g : 1);
-}
-
-void conv3(const ConvArgs& a, int mode, hipStream_t s) {
-  const size_t P = (size_t)a.B * a.H * a.W;
-  const unsigned ngroups = (unsigned)((a.nout + 63) / 64);
-  if (P >= CONV_TILED_MIN_PIXELS) {
-    // widest channel group (16 NT, NT <= 4) that divides cout
-    const int t16 = a.nout / 16;
-    const int nt = t16 % 4 == 0 ? 4 : t16 % 3 == 0 ? 3 : t16 % 2 == 0 ? 2 : 1;
-    const dim3 grid((unsigned)(a.B * ((a.H + 15) / 16) * ((a.W + 15) / 16) * (t16 / nt)));
-    switch (mode * 4 + nt - 1) {
-#define KP_HALO_CASE(M, N) \
-  case M * 4 + N - 1: hipLaunchKernelGGL((k_conv3_halo<M, N>), grid, dim3(256), 0, s, a); break;
-      KP_HALO_CASE(CONV_RELU, 1) KP_HALO_CASE(CONV_RELU, 2) KP_HALO_CASE(CONV_RELU, 3) KP_HALO_CASE(CONV_RELU, 4)
-      KP_HALO_CASE(CONV_LINEAR, 1) KP_HALO_CASE(CONV_LINEAR, 2) KP_HALO_CASE(CONV_LINEAR, 3)
-      KP_HALO_CASE(CONV_LINEAR, 4) KP_HALO_CASE(CONV_MASK, 1) KP_HALO_CASE(CONV_MASK, 2)
-      KP_HALO_CASE(CONV_MASK, 3) KP_HALO_CASE(CONV_MASK, 4)
-#undef KP_HALO_CASE
-    }
-    return;
-  }
-  const size_t waves = ((P + 31) / 32) * ngroups;
-  const dim3 grid((unsigned)((waves + 3) / 4));
-  if (mode == CONV_RELU) hipLaunchKernelGGL(k_conv3<CONV_RELU>, grid, dim3(256), 0, s, a);
-  else if (mode == CONV_LINEAR) hipLaunchKernelGGL(k_conv3<CONV_LINEAR>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_conv3<CONV_MASK>, grid, dim3(256), 0, s, a);
 }
 
 WgradPlan wgrad_plan(int cout, int cin, size_t P) {

@@ -55,7 +55,7 @@ struct Work {
   int32_t* aug;
 };
 
-constexpr int NEVENT = 512;  // 8 averaged passes of a 6-level network record 354
+constexpr int NEVENT = 256;  // 8 averaged passes of a 6-level network record at most 178
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -83,6 +83,8 @@ struct kp_dn {
   struct Mark { int a, b, cat; double flop; };
   std::vector<Mark> marks;
   int nev = 0;
+  int ev_conv = -1;  // mark of the run of convolutions being launched
+  double flop_conv = 0.0;
   int ev_total0 = -1, ev_total1 = -1;
   // layer index of encoder block l, the bottleneck and decoder block l (conv a; b = +1)
   int E(int l) const { return 2 * l; }
@@ -131,7 +133,22 @@ void mark_end(kp_dn* dn, int e, int cat, double flop, hipStream_t s) {
 void marks_reset(kp_dn* dn) {
   dn->marks.clear();
   dn->nev = 0;
+  dn->ev_conv = -1;
   dn->ev_total0 = dn->ev_total1 = -1;
+}
+
+// convolutions launched one after the other share a pair of events (a pair
+// costs the stream about as much as a small kernel)
+void conv_mark(kp_dn* dn, double flop, hipStream_t s) {
+  if (dn->ev_conv < 0) {
+    dn->ev_conv = mark_begin(dn, s);
+    dn->flop_conv = 0.0;
+  }
+  dn->flop_conv += flop;
+}
+void conv_done(kp_dn* dn, hipStream_t s) {
+  mark_end(dn, dn->ev_conv, CAT_CONV, dn->flop_conv, s);
+  dn->ev_conv = -1;
 }
 
 // --- workspace -------------------------------------------------------------------
@@ -229,7 +246,19 @@ kp_status check_maps(kp_dn* dn, const void* a, const void* b, int32_t B, int32_t
 // --- network schedule --------------------------------------------------------------
 double conv_flop(const Layer& y, size_t P) { return 2.0 * (double)P * 9.0 * y.cin_true * y.cout; }
 
-void conv_fwd(kp_dn* dn, int l, const uint16_t* x, int xs, uint16_t* y, int ys, int B, int H, int W, hipStream_t s) {
+// a map at half resolution that stands in for the first channels of a layer's
+// input, and where the 2x2 means of its output go
+struct Low {
+  const uint16_t* x = nullptr;
+  int xs = 0, c = 0;
+};
+struct Means {
+  uint16_t* y = nullptr;
+  int ys = 0;
+};
+
+void conv_fwd(kp_dn* dn, int l, const uint16_t* x, int xs, uint16_t* y, int ys, int B, int H, int W, hipStream_t s,
+              Low low = {}, Means means = {}) {
   const Layer& L = dn->layers[l];
   ConvArgs a{};
   a.x = x;
@@ -244,9 +273,13 @@ void conv_fwd(kp_dn* dn, int l, const uint16_t* x, int xs, uint16_t* y, int ys, 
   a.B = B;
   a.H = H;
   a.W = W;
-  const int e = mark_begin(dn, s);
+  a.xl = low.x;
+  a.xls = low.xs;
+  a.cl = low.c;
+  a.yp = means.y;
+  a.yps = means.ys;
+  conv_mark(dn, conv_flop(L, (size_t)B * H * W), s);
   conv3(a, CONV_RELU, s);
-  mark_end(dn, e, CAT_CONV, conv_flop(L, (size_t)B * H * W), s);
 }
 
 // input gradient of layer l: gx (stride gxs) from gz (stride cout), zero where mask <= 0
@@ -267,12 +300,12 @@ void conv_dgrad(kp_dn* dn, int l, const uint16_t* gz, uint16_t* gx, int gxs, con
   a.B = B;
   a.H = H;
   a.W = W;
-  const int e = mark_begin(dn, s);
-  conv3(a, CONV_MASK, s);
-  mark_end(dn, e, CAT_CONV, conv_flop(L, (size_t)B * H * W), s);
+  conv_mark(dn, conv_flop(L, (size_t)B * H * W), s);
+  conv3(a, mask ? CONV_MASK : CONV_PLAIN, s);
 }
 
-void conv_wgrad(kp_dn* dn, int l, const uint16_t* gz, const uint16_t* x, int xs, int B, int H, int W, hipStream_t s) {
+void conv_wgrad(kp_dn* dn, int l, const uint16_t* gz, const uint16_t* x, int xs, int B, int H, int W, hipStream_t s,
+                Low low = {}) {
   const Layer& L = dn->layers[l];
   WgradArgs a{};
   a.gz = gz;
@@ -282,15 +315,30 @@ void conv_wgrad(kp_dn* dn, int l, const uint16_t* gz, const uint16_t* x, int xs,
   a.xs = xs;
   a.cin = L.cin;
   a.cin_true = L.cin_true;
+  a.xl = low.x;
+  a.xls = low.xs;
+  a.cl = low.c;
   a.gw = dn->d_g + L.w_off;
   a.gb = dn->d_g + L.b_off;
   a.part = dn->w.wpart;
   a.B = B;
   a.H = H;
   a.W = W;
+  conv_done(dn, s);
   const int e = mark_begin(dn, s);
   wgrad(a, s);
   mark_end(dn, e, CAT_WGRAD, conv_flop(L, (size_t)B * H * W), s);
+}
+
+// whether decoder level l reads the map below in place instead of an upsampled
+// copy in cat[l]: the tiled convolution takes it in blocks of 32 channels (its
+// weight gradient, where cin >= WH_MIN_CIN, in chunks of 8)
+bool low_in_place(const kp_dn* dn, int l, size_t P) {
+  return conv_tiled(P) && dn->c[l + 1] % 32 == 0 && dn->c[l + 1] + dn->c[l] >= WH_MIN_CIN;
+}
+Low map_below(const kp_dn* dn, int l, size_t P) {
+  if (!low_in_place(dn, l, P)) return {};
+  return {l + 1 < dn->L - 1 ? dn->w.dout[l + 1] : dn->w.mout, dn->c[l + 1], dn->c[l + 1]};
 }
 
 // maps -> w.out (network output: predicted fractions q', u'); activations kept
@@ -303,6 +351,7 @@ kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, in
   const size_t P1 = (size_t)B * H * W;
   auto Hl = [&](int l) { return H >> l; };
   auto Wl = [&](int l) { return W >> l; };
+  auto Pl = [&](int l) { return (size_t)B * (H >> l) * (W >> l); };
   zero(w.sum, (size_t)B * 16, s);
   sums(maps, B, H * W, dn->runs, w.sum, s);
   prep(maps, target, w.sum, use_aug ? w.aug : nullptr, code_all, B, H, W, dn->runs, w.x0, w.xq, w.ihat, w.tgt, s);
@@ -311,8 +360,13 @@ kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, in
     const uint16_t* in = l == 0 ? w.x0 : w.pool[l];
     const int ins = l == 0 ? 8 : c[l - 1];
     conv_fwd(dn, dn->E(l), in, ins, w.ea[l], c[l], B, Hl(l), Wl(l), s);
-    conv_fwd(dn, dn->E(l) + 1, w.ea[l], c[l], w.cat[l] + c[l + 1], c[l + 1] + c[l], B, Hl(l), Wl(l), s);
-    pool(w.cat[l] + c[l + 1], c[l + 1] + c[l], w.pool[l + 1], c[l], B, Hl(l), Wl(l), c[l], s);
+    const bool means = conv_tiled(Pl(l));
+    conv_fwd(dn, dn->E(l) + 1, w.ea[l], c[l], w.cat[l] + c[l + 1], c[l + 1] + c[l], B, Hl(l), Wl(l), s, {},
+             means ? Means{w.pool[l + 1], c[l]} : Means{});
+    if (!means) {
+      conv_done(dn, s);
+      pool(w.cat[l] + c[l + 1], c[l + 1] + c[l], w.pool[l + 1], c[l], B, Hl(l), Wl(l), c[l], s);
+    }
   }
   // bottleneck
   conv_fwd(dn, dn->M(), w.pool[L - 1], c[L - 2], w.ma, c[L - 1], B, Hl(L - 1), Wl(L - 1), s);
@@ -321,12 +375,17 @@ kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, in
   const uint16_t* below = w.mout;
   int bs = c[L - 1];
   for (int l = L - 2; l >= 0; --l) {
-    up(below, bs, w.cat[l], c[l + 1] + c[l], B, Hl(l), Wl(l), c[l + 1], s);
-    conv_fwd(dn, dn->D(l), w.cat[l], c[l + 1] + c[l], w.da[l], c[l], B, Hl(l), Wl(l), s);
+    const Low low = map_below(dn, l, Pl(l));
+    if (!low.x) {
+      conv_done(dn, s);
+      up(below, bs, w.cat[l], c[l + 1] + c[l], B, Hl(l), Wl(l), c[l + 1], s);
+    }
+    conv_fwd(dn, dn->D(l), w.cat[l], c[l + 1] + c[l], w.da[l], c[l], B, Hl(l), Wl(l), s, low);
     conv_fwd(dn, dn->D(l) + 1, w.da[l], c[l], w.dout[l], c[l], B, Hl(l), Wl(l), s);
     below = w.dout[l];
     bs = c[l];
   }
+  conv_done(dn, s);
   head(w.dout[0], c[0], dn->d_p + dn->head_w, dn->d_p + dn->head_b, w.xq, w.out, P1, s);
   DN_HIP(hipGetLastError(), "denoiser forward launch");
   return KP_OK;
@@ -339,6 +398,7 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
   const size_t P1 = (size_t)B * H * W;
   auto Hl = [&](int l) { return H >> l; };
   auto Wl = [&](int l) { return W >> l; };
+  auto Pl = [&](int l) { return (size_t)B * (H >> l) * (W >> l); };
   zero(dn->d_g, dn->n_params * 4, s);
   zero(w.loss, 8, s);
   loss(w.out, w.tgt, w.ihat, w.sum, B, H * W, w.go, w.loss, s);
@@ -349,8 +409,9 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
     const int cc = c[l + 1] + c[l];
     conv_wgrad(dn, dn->D(l) + 1, w.gd[l], w.da[l], c[l], B, Hl(l), Wl(l), s);
     conv_dgrad(dn, dn->D(l) + 1, w.gd[l], w.gdb[l], c[l], w.da[l], c[l], B, Hl(l), Wl(l), s);
-    conv_wgrad(dn, dn->D(l), w.gdb[l], w.cat[l], cc, B, Hl(l), Wl(l), s);
+    conv_wgrad(dn, dn->D(l), w.gdb[l], w.cat[l], cc, B, Hl(l), Wl(l), s, map_below(dn, l, Pl(l)));
     conv_dgrad(dn, dn->D(l), w.gdb[l], w.gcat[l], cc, nullptr, 0, B, Hl(l), Wl(l), s);
+    conv_done(dn, s);
     // gradient of the block below's output: adjoint of up, masked by its relu
     if (l + 1 < L - 1) up_bwd(w.gcat[l], cc, w.gd[l + 1], c[l + 1], w.dout[l + 1], c[l + 1], B, Hl(l), Wl(l), c[l + 1], s);
     else up_bwd(w.gcat[l], cc, w.gm, c[L - 1], w.mout, c[L - 1], B, Hl(l), Wl(l), c[L - 1], s);
@@ -360,6 +421,7 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
   conv_dgrad(dn, dn->M() + 1, w.gm, w.gmb, c[L - 1], w.ma, c[L - 1], B, Hl(L - 1), Wl(L - 1), s);
   conv_wgrad(dn, dn->M(), w.gmb, w.pool[L - 1], c[L - 2], B, Hl(L - 1), Wl(L - 1), s);
   conv_dgrad(dn, dn->M(), w.gmb, w.gpool[L - 1], c[L - 2], nullptr, 0, B, Hl(L - 1), Wl(L - 1), s);
+  conv_done(dn, s);
   // encoder, coarsest level first: skip gradient plus the pooled path
   for (int l = L - 2; l >= 0; --l) {
     const int cc = c[l + 1] + c[l];
@@ -370,6 +432,7 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
     if (l > 0) {
       conv_wgrad(dn, dn->E(l), w.geb[l], w.pool[l], c[l - 1], B, Hl(l), Wl(l), s);
       conv_dgrad(dn, dn->E(l), w.geb[l], w.gpool[l], c[l - 1], nullptr, 0, B, Hl(l), Wl(l), s);
+      conv_done(dn, s);
     } else {
       conv_wgrad(dn, dn->E(0), w.geb[0], w.x0, 8, B, H, W, s);
     }

@@ -8,10 +8,11 @@
 namespace kp {
 namespace dn {
 
-enum { CONV_RELU = 0, CONV_LINEAR = 1, CONV_MASK = 2 };
+enum { CONV_RELU = 0, CONV_PLAIN = 1, CONV_MASK = 2 };
 
-// pixel count from which convolutions use the LDS-tiled kernel (256 pixels per workgroup)
-constexpr size_t CONV_TILED_MIN_PIXELS = 1024;  // from here on the LDS-staged kernel
+// pixel count from which convolutions use the LDS-tiled kernel
+constexpr size_t CONV_TILED_MIN_PIXELS = 1024;
+inline bool conv_tiled(size_t P) { return P >= CONV_TILED_MIN_PIXELS; }
 
 // y[p][n] (stride ys) from x[p][c] (stride xs, cin channels per tap, cin % 8 == 0)
 // and GEMM weights w[nout][kp] (kp % 32 == 0, kp >= 9 cin, nout % 16 == 0).
@@ -20,12 +21,17 @@ struct ConvArgs {
   int xs, cin;
   const uint16_t* w;
   int kp, nout;
-  const float* bias;     // CONV_RELU / CONV_LINEAR
+  const float* bias;     // CONV_RELU
   uint16_t* y;
   int ys;
-  const uint16_t* mask;  // CONV_MASK: zero the output where mask[p][n] <= 0 (none if null)
+  const uint16_t* mask;  // CONV_MASK: zero the output where mask[p][n] <= 0
   int ms;
   int B, H, W;
+  // only where conv_tiled(B H W):
+  const uint16_t* xl;  // if set, channels 0..cl-1 (cl % 32 == 0) come from this map at half
+  int xls, cl;         // resolution (stride xls), each pixel standing for a 2x2 block; x holds the rest
+  uint16_t* yp;        // CONV_RELU: if set, the 2x2 means of y at half resolution (stride yps; H, W even)
+  int yps;
 };
 
 // gw[cout][9][cin_true] += gradient of a conv layer's weights from the
@@ -36,6 +42,8 @@ struct WgradArgs {
   int gzs, cout;
   const uint16_t* x;
   int xs, cin, cin_true;
+  const uint16_t* xl;  // as ConvArgs::xl (cl % 8 == 0; where cin >= WH_MIN_CIN)
+  int xls, cl;
   float* gw;  // weight gradient [cout][9][cin_true], accumulated
   float* gb;  // bias gradient [cout], accumulated
   float* part;  // k_wgrad_halo's partial blocks, wgrad_part_floats(cout, cin) floats
@@ -48,6 +56,7 @@ struct WgradArgs {
 constexpr int WG_SLAB = 128;        // pixels per LDS slab
 constexpr int WG_TARGET = 1024;     // workgroups per launch to aim for
 constexpr int WG_MIN_CHUNK = 1024;  // fewest pixels per chunk
+constexpr int WH_MIN_CIN = 48;      // narrower inputs keep k_wgrad
 struct WgradPlan {
   int ktiles, mtiles, nch, chunk;
 };
