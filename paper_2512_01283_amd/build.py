@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpolrad.so")
 ARCH = "gfx950"
 
-SOURCES = ["kp_kernels.hip", "kp_image.hip", "kp_api.cpp", "kp_conv.hip", "kp_denoiser.hip", "kp_dn_api.cpp"]
+SOURCES = ["kp_kernels.hip", "kp_image.hip", "kp_api.cpp", "kp_conv.hip", "kp_wgrad.hip", "kp_denoiser.hip", "kp_dn_api.cpp"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -38,6 +38,8 @@ SOURCE_FLAGS = {
     "kp_kernels.hip": ["-mllvm", "-disable-machine-licm", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
     "kp_image.hip": ["-mllvm", "-disable-machine-licm"],
     # accumulators in ordinary registers: in the others they are copied back and forth around every epilogue
+    # the operands' addresses in the second LDS buffer are not worth registers kept over the loop
+    "kp_wgrad.hip": ["-mllvm", "-disable-machine-licm"],
     "kp_conv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 

@@ -50,7 +50,7 @@ struct Work {
            *geb[MAX_LEVELS] = {}, *gpool[MAX_LEVELS] = {};
   uint16_t *gm = nullptr, *gmb = nullptr;
   float *xq, *ihat, *tgt, *out, *go;
-  float* wpart = nullptr;  // partial weight-gradient blocks (k_wgrad_halo)
+  float* wpart = nullptr;  // partial weight-gradient blocks
   double *sum, *loss;
   int32_t* aug;
 };
@@ -192,9 +192,20 @@ kp_status ensure_work(kp_dn* dn, size_t P1, int B) {
   plan.push_back({(void**)&w.sum, (size_t)bcap * 16});
   plan.push_back({(void**)&w.loss, 8});
   plan.push_back({(void**)&w.aug, (size_t)bcap * 4});
-  size_t part = 0;
-  for (const Layer& y : dn->layers) part = std::max(part, wgrad_part_floats(y.cout, y.cin));
-  plan.push_back({(void**)&w.wpart, part * 4});
+  WgradLayer wl[WGRAD_MAX];
+  int nwl = 0;
+  for (size_t k = 0; k < dn->layers.size(); ++k) {
+    // a layer taken in two ranges (map below, skip) has the blocks of both
+    const Layer& y = dn->layers[k];
+    const bool dec = (int)k > dn->M() + 1 && k % 2 == 0;
+    wl[nwl].cout = y.cout;
+    wl[nwl++].cin = dec ? y.cin - y.cout : y.cin;
+    if (dec) {
+      wl[nwl].cout = y.cout;
+      wl[nwl++].cin = y.cout;
+    }
+  }
+  plan.push_back({(void**)&w.wpart, wgrad_part_floats(wl, nwl) * 4});
   std::vector<size_t> offs;
   for (auto& e : plan) {
     offs.push_back(off);
@@ -304,40 +315,10 @@ void conv_dgrad(kp_dn* dn, int l, const uint16_t* gz, uint16_t* gx, int gxs, con
   conv3(a, mask ? CONV_MASK : CONV_PLAIN, s);
 }
 
-void conv_wgrad(kp_dn* dn, int l, const uint16_t* gz, const uint16_t* x, int xs, int B, int H, int W, hipStream_t s,
-                Low low = {}) {
-  const Layer& L = dn->layers[l];
-  WgradArgs a{};
-  a.gz = gz;
-  a.gzs = L.cout;
-  a.cout = L.cout;
-  a.x = x;
-  a.xs = xs;
-  a.cin = L.cin;
-  a.cin_true = L.cin_true;
-  a.xl = low.x;
-  a.xls = low.xs;
-  a.cl = low.c;
-  a.gw = dn->d_g + L.w_off;
-  a.gb = dn->d_g + L.b_off;
-  a.part = dn->w.wpart;
-  a.B = B;
-  a.H = H;
-  a.W = W;
-  conv_done(dn, s);
-  const int e = mark_begin(dn, s);
-  wgrad(a, s);
-  mark_end(dn, e, CAT_WGRAD, conv_flop(L, (size_t)B * H * W), s);
-}
-
-// whether decoder level l reads the map below in place instead of an upsampled
-// copy in cat[l]: the tiled convolution takes it in blocks of 32 channels (its
-// weight gradient, where cin >= WH_MIN_CIN, in chunks of 8)
-bool low_in_place(const kp_dn* dn, int l, size_t P) {
-  return conv_tiled(P) && dn->c[l + 1] % 32 == 0 && dn->c[l + 1] + dn->c[l] >= WH_MIN_CIN;
-}
+// the map below as decoder level l reads it in place; none where it takes an
+// upsampled copy in cat[l] (the tiled convolution reads blocks of 32 channels)
 Low map_below(const kp_dn* dn, int l, size_t P) {
-  if (!low_in_place(dn, l, P)) return {};
+  if (!conv_tiled(P) || dn->c[l + 1] % 32) return {};
   return {l + 1 < dn->L - 1 ? dn->w.dout[l + 1] : dn->w.mout, dn->c[l + 1], dn->c[l + 1]};
 }
 
@@ -391,6 +372,41 @@ kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, in
   return KP_OK;
 }
 
+// the weight-gradient jobs of a backward pass: every gz and input they read stays to its end
+struct Wgrads {
+  WgradLayer l[WGRAD_MAX];
+  int n = 0;
+  double flop = 0.0;
+  void add(const kp_dn* dn, int k, const uint16_t* gz, const uint16_t* x, int xs, int B, int H, int W, Low low = {}) {
+    const Layer& L = dn->layers[k];
+    WgradLayer a{};
+    a.gz = gz;
+    a.gzs = a.cout = L.cout;
+    a.gws = L.cin_true;
+    a.B = B;
+    a.H = H;
+    a.W = W;
+    a.gb = dn->d_g + L.b_off;
+    a.gw = dn->d_g + L.w_off;
+    if (low.x) {
+      a.x = low.x;
+      a.xs = low.xs;
+      a.cin = a.cin_true = low.c;
+      a.low = 1;
+      l[n++] = a;
+      a.gb = nullptr;
+      a.gw += low.c;
+      a.low = 0;
+    }
+    a.x = x + low.c;
+    a.xs = xs;
+    a.cin = L.cin - low.c;
+    a.cin_true = L.cin_true - low.c;
+    l[n++] = a;
+    flop += conv_flop(L, (size_t)B * H * W);
+  }
+};
+
 kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
   Work& w = dn->w;
   const int L = dn->L;
@@ -404,12 +420,13 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
   loss(w.out, w.tgt, w.ihat, w.sum, B, H * W, w.go, w.loss, s);
   head_bwd(w.go, w.dout[0], c[0], dn->d_p + dn->head_w, dn->d_g + dn->head_w, dn->d_g + dn->head_b, w.gd[0], P1,
            s);
+  Wgrads wg;
   // decoder, finest level first
   for (int l = 0; l < L - 1; ++l) {
     const int cc = c[l + 1] + c[l];
-    conv_wgrad(dn, dn->D(l) + 1, w.gd[l], w.da[l], c[l], B, Hl(l), Wl(l), s);
+    wg.add(dn, dn->D(l) + 1, w.gd[l], w.da[l], c[l], B, Hl(l), Wl(l));
     conv_dgrad(dn, dn->D(l) + 1, w.gd[l], w.gdb[l], c[l], w.da[l], c[l], B, Hl(l), Wl(l), s);
-    conv_wgrad(dn, dn->D(l), w.gdb[l], w.cat[l], cc, B, Hl(l), Wl(l), s, map_below(dn, l, Pl(l)));
+    wg.add(dn, dn->D(l), w.gdb[l], w.cat[l], cc, B, Hl(l), Wl(l), map_below(dn, l, Pl(l)));
     conv_dgrad(dn, dn->D(l), w.gdb[l], w.gcat[l], cc, nullptr, 0, B, Hl(l), Wl(l), s);
     conv_done(dn, s);
     // gradient of the block below's output: adjoint of up, masked by its relu
@@ -417,9 +434,9 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
     else up_bwd(w.gcat[l], cc, w.gm, c[L - 1], w.mout, c[L - 1], B, Hl(l), Wl(l), c[L - 1], s);
   }
   // bottleneck
-  conv_wgrad(dn, dn->M() + 1, w.gm, w.ma, c[L - 1], B, Hl(L - 1), Wl(L - 1), s);
+  wg.add(dn, dn->M() + 1, w.gm, w.ma, c[L - 1], B, Hl(L - 1), Wl(L - 1));
   conv_dgrad(dn, dn->M() + 1, w.gm, w.gmb, c[L - 1], w.ma, c[L - 1], B, Hl(L - 1), Wl(L - 1), s);
-  conv_wgrad(dn, dn->M(), w.gmb, w.pool[L - 1], c[L - 2], B, Hl(L - 1), Wl(L - 1), s);
+  wg.add(dn, dn->M(), w.gmb, w.pool[L - 1], c[L - 2], B, Hl(L - 1), Wl(L - 1));
   conv_dgrad(dn, dn->M(), w.gmb, w.gpool[L - 1], c[L - 2], nullptr, 0, B, Hl(L - 1), Wl(L - 1), s);
   conv_done(dn, s);
   // encoder, coarsest level first: skip gradient plus the pooled path
@@ -427,16 +444,20 @@ kp_status backward(kp_dn* dn, int B, int H, int W, hipStream_t s) {
     const int cc = c[l + 1] + c[l];
     pool_bwd_add(w.gcat[l] + c[l + 1], cc, w.gpool[l + 1], c[l], w.cat[l] + c[l + 1], cc, w.ge[l], c[l], B, Hl(l),
                  Wl(l), c[l], s);
-    conv_wgrad(dn, dn->E(l) + 1, w.ge[l], w.ea[l], c[l], B, Hl(l), Wl(l), s);
+    wg.add(dn, dn->E(l) + 1, w.ge[l], w.ea[l], c[l], B, Hl(l), Wl(l));
     conv_dgrad(dn, dn->E(l) + 1, w.ge[l], w.geb[l], c[l], w.ea[l], c[l], B, Hl(l), Wl(l), s);
     if (l > 0) {
-      conv_wgrad(dn, dn->E(l), w.geb[l], w.pool[l], c[l - 1], B, Hl(l), Wl(l), s);
+      wg.add(dn, dn->E(l), w.geb[l], w.pool[l], c[l - 1], B, Hl(l), Wl(l));
       conv_dgrad(dn, dn->E(l), w.geb[l], w.gpool[l], c[l - 1], nullptr, 0, B, Hl(l), Wl(l), s);
       conv_done(dn, s);
     } else {
-      conv_wgrad(dn, dn->E(0), w.geb[0], w.x0, 8, B, H, W, s);
+      wg.add(dn, dn->E(0), w.geb[0], w.x0, 8, B, H, W);
     }
   }
+  conv_done(dn, s);
+  const int e = mark_begin(dn, s);
+  wgrad(wg.l, wg.n, w.wpart, s);
+  mark_end(dn, e, CAT_WGRAD, wg.flop, s);
   DN_HIP(hipGetLastError(), "denoiser backward launch");
   return KP_OK;
 }

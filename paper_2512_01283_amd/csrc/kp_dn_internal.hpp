@@ -34,42 +34,40 @@ struct ConvArgs {
   int yps;
 };
 
-// gw[cout][9][cin_true] += gradient of a conv layer's weights from the
-// gradient gz[p][co] (stride gzs) of its pre-activation output and its input
-// x[p][c] (stride xs, cin channels per tap, cin % 8 == 0, cout % 16 == 0).
-struct WgradArgs {
+// One layer's weight and bias gradients, or those of a channel range of its
+// input: gw[co][kk][c] (rows of gws floats per tap, c < cin_true) and gb[co]
+// += the gradients from gz[p][co] (stride gzs), the gradient of the layer's
+// pre-activation output, and its input x[p][c] (stride xs, cin channels,
+// cin % 8 == 0, cout % 16 == 0).
+struct WgradLayer {
   const uint16_t* gz;
   int gzs, cout;
   const uint16_t* x;
-  int xs, cin, cin_true;
-  const uint16_t* xl;  // as ConvArgs::xl (cl % 8 == 0; where cin >= WH_MIN_CIN)
-  int xls, cl;
-  float* gw;  // weight gradient [cout][9][cin_true], accumulated
-  float* gb;  // bias gradient [cout], accumulated
-  float* part;  // k_wgrad_halo's partial blocks, wgrad_part_floats(cout, cin) floats
+  int xs, cin, cin_true, gws;
+  int low;    // x lies at half resolution, each pixel standing for a 2x2 block (H, W even)
+  float* gw;
+  float* gb;  // null: another range's job
   int B, H, W;
-  int chunk, nch, ktiles, mtiles;  // set by the launcher
+  // set by the launcher: blocks of output channels; blocks of 64, 32 and 16
+  // input channels and their pixel chunks; first workgroup, first block of
+  // sums, first float of scratch
+  int mt, units[3], nch[3], first, sum_first;
+  size_t part;
 };
-
-// Weight-gradient work split: 64 x 64 (cout, 9 cin) tiles times nch pixel
-// chunks of `chunk` pixels.
-constexpr int WG_SLAB = 128;        // pixels per LDS slab
-constexpr int WG_TARGET = 1024;     // workgroups per launch to aim for
-constexpr int WG_MIN_CHUNK = 1024;  // fewest pixels per chunk
-constexpr int WH_MIN_CIN = 48;      // narrower inputs keep k_wgrad
-struct WgradPlan {
-  int ktiles, mtiles, nch, chunk;
+constexpr int WGRAD_MAX = 27;  // 22 layers of a 6-level network, 5 of them in two ranges
+struct WgradBatch {
+  WgradLayer l[WGRAD_MAX];
+  int n, wgs, sums;
+  float* part;
 };
-WgradPlan wgrad_plan(int cout, int cin, size_t P);
-// k_wgrad_halo (cin >= 48): 64 x 64 (co, c) channel tiles times nch chunks of
-// `chunk` pixel tiles of 8 x 16
-WgradPlan wgrad_halo_plan(int cout, int cin, int B, int H, int W);
-// scratch of the partial blocks k_wgrad_halo writes for a layer at any image
-// size (0 where the layer keeps k_wgrad)
-size_t wgrad_part_floats(int cout, int cin);
+// floats of a partial block: 16 mr x 9 x 16 g weights, 16 mr biases
+__host__ __device__ constexpr size_t wgrad_block_floats(int mr, int g) { return (size_t)16 * mr * (9 * 16 * g + 1); }
+// scratch for these layers (cin, cout) at any image size
+size_t wgrad_part_floats(const WgradLayer* l, int n);
+// the gradients of n <= WGRAD_MAX layers
+void wgrad(const WgradLayer* l, int n, float* part, hipStream_t s);
 
 void conv3(const ConvArgs& a, int mode, hipStream_t s);
-void wgrad(WgradArgs a, hipStream_t s);
 void pool(const uint16_t* x, int xs, uint16_t* y, int ys, int B, int H, int W, int C, hipStream_t s);
 void up(const uint16_t* x, int xs, uint16_t* y, int ys, int B, int H, int W, int C, hipStream_t s);
 void up_bwd(const uint16_t* gy, int gys, uint16_t* gx, int gxs, const uint16_t* mask, int ms, int B, int H, int W,
