@@ -187,10 +187,9 @@ __device__ __forceinline__ void dihedral_source(int code, int H, int W, int& h, 
   sv = f ? -1.0 : 1.0;
 }
 
-// code_all >= 0 (with aug == nullptr) applies that one element to every image.
 __global__ void k_prep(const double* __restrict__ maps, const double* __restrict__ target,
-                       const double* __restrict__ sums, const int32_t* __restrict__ aug, int code_all, int B, int H,
-                       int W, int runs, uint16_t* __restrict__ x, float* __restrict__ xq, float* __restrict__ ihat,
+                       const double* __restrict__ sums, const int32_t* __restrict__ aug, int B, int H, int W,
+                       int runs, uint16_t* __restrict__ x, float* __restrict__ xq, float* __restrict__ ihat,
                        float* __restrict__ tgt) {
   const int HW = H * W;
   const size_t n = (size_t)B * HW;
@@ -199,7 +198,6 @@ __global__ void k_prep(const double* __restrict__ maps, const double* __restrict
     int h = (int)(k % HW) / W, w = (int)(k % HW) % W;
     double sq = 1.0, su = 1.0, sv = 1.0;
     if (aug) dihedral_source(aug[b], H, W, h, w, sq, su, sv);
-    else if (code_all >= 0) dihedral_source(code_all, H, W, h, w, sq, su, sv);
     const size_t p = (size_t)h * W + w;
     const double mean = sums[2 * b] / HW;
     const double* m = maps + b * 4 * runs * HW + p;
@@ -233,6 +231,27 @@ __global__ void k_prep(const double* __restrict__ maps, const double* __restrict
   }
 }
 
+// Features of the images transformed by `code`, from those of the images as
+// they are: the pixel dihedral_source names, with the signs of Q, U and V
+// (their BF16 sign bits) flipped as it says.  An averaged inference prepares
+// its features once and turns them (5 us for eight 256^2 maps, where forming
+// them again took 18 and their sums 11).
+__global__ void k_turn(const uint16_t* __restrict__ x, int B, int H, int W, int code, uint16_t* __restrict__ y) {
+  const int HW = H * W;
+  const size_t n = (size_t)B * HW;
+  for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
+    const size_t b = k / HW;
+    int h = (int)(k % HW) / W, w = (int)(k % HW) % W;
+    double sq, su, sv;
+    dihedral_source(code, H, W, h, w, sq, su, sv);
+    u32x4 v = ld16(x + (b * HW + (size_t)h * W + w) * 8);
+    if (sq < 0.0) v[0] ^= 0x80000000u;
+    if (su < 0.0) v[1] ^= 0x8000u;
+    if (sv < 0.0) v[1] ^= 0x80000000u;
+    st16(y + k * 8, v);
+  }
+}
+
 // out[p][o] = xq[p][o] + hb[o] + sum_c d[p][c] hw[o][c]   (C % 8 == 0)
 // Eight lanes per pixel: lane g of a group reads channels 8g + 64i (16 bytes
 // each), so a group's loads of one pixel are contiguous and each load
@@ -240,9 +259,18 @@ __global__ void k_prep(const double* __restrict__ maps, const double* __restrict
 // every instruction touched 64 lines for 16 bytes of each: 3.5x slower).
 // The partial sums meet by lane shuffles inside the group; all eight lanes
 // of a group take the same p, so a shuffle never reads an inactive lane.
+// With TURN the pixels are those of images transformed by `code`, xq belongs
+// to the images as they are, and the fractions (q', u') go back to their source
+// pixels with the inverse signs (the signs are their own inverses): out[src],
+// in the original pixel order, is set if first and added to otherwise.  The
+// transform is a bijection of each image's pixels: no two groups write the
+// same element.
+template <bool TURN>
 __global__ void k_head(const uint16_t* __restrict__ d, int C, const float* __restrict__ hw,
-                       const float* __restrict__ hb, const float* __restrict__ xq, float* __restrict__ out, size_t P) {
-  const int g = threadIdx.x & 7;
+                       const float* __restrict__ hb, const float* __restrict__ xq, float* __restrict__ out, int B,
+                       int H, int W, int code, int first) {
+  const int g = threadIdx.x & 7, HW = H * W;
+  const size_t P = (size_t)B * HW;
   const size_t stride = ((size_t)gridDim.x * blockDim.x) >> 3;
   for (size_t p = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3; p < P; p += stride) {
     float a0 = 0.f, a1 = 0.f;
@@ -261,8 +289,20 @@ __global__ void k_head(const uint16_t* __restrict__ d, int C, const float* __res
       a1 += __shfl_xor(a1, off);
     }
     if (g == 0) {
-      out[2 * p] = xq[2 * p] + hb[0] + a0;
-      out[2 * p + 1] = xq[2 * p + 1] + hb[1] + a1;
+      if constexpr (TURN) {
+        const size_t b = p / HW;
+        int h = (int)(p % HW) / W, w = (int)(p % HW) % W;
+        double dq, du, dv;
+        dihedral_source(code, H, W, h, w, dq, du, dv);
+        const float sq = (float)dq, su = (float)du;
+        const size_t src = b * HW + (size_t)h * W + w;
+        const float q = sq * (sq * xq[2 * src] + hb[0] + a0), u = su * (su * xq[2 * src + 1] + hb[1] + a1);
+        out[2 * src] = first ? q : out[2 * src] + q;
+        out[2 * src + 1] = first ? u : out[2 * src + 1] + u;
+      } else {
+        out[2 * p] = xq[2 * p] + hb[0] + a0;
+        out[2 * p + 1] = xq[2 * p + 1] + hb[1] + a1;
+      }
     }
   }
 }
@@ -349,28 +389,6 @@ __global__ void k_head_bwd(const float* __restrict__ go, const uint16_t* __restr
   __syncthreads();
   for (int k = tid; k < 2 * C; k += 256) atomicAdd(ghw + k, red[k]);
   if (tid < 2) atomicAdd(ghb + tid, red[2 * C + tid]);
-}
-
-// Test-time averaging: out holds the network's fractions (q', u') of the
-// images transformed by `code`; each is moved back to its source pixel with
-// the inverse Stokes signs (the signs are their own inverses) and added to
-// acc ([B][HW][2] in the original pixel order), or stored there if first.
-// The transform is a bijection of each image's pixels: no two threads write
-// the same element.
-__global__ void k_tta_acc(const float* __restrict__ out, int B, int H, int W, int code, int first,
-                          float* __restrict__ acc) {
-  const int HW = H * W;
-  const size_t n = (size_t)B * HW;
-  for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-    const size_t b = k / HW;
-    int h = (int)(k % HW) / W, w = (int)(k % HW) % W;
-    double sq, su, sv;
-    dihedral_source(code, H, W, h, w, sq, su, sv);
-    const size_t src = b * HW + (size_t)h * W + w;
-    const float q = (float)sq * out[2 * k], u = (float)su * out[2 * k + 1];
-    acc[2 * src] = first ? q : acc[2 * src] + q;
-    acc[2 * src + 1] = first ? u : acc[2 * src + 1] + u;
-  }
 }
 
 // denoised maps: I and V from the input (the two runs' mean if runs == 2),
@@ -460,14 +478,19 @@ void pool_bwd_add(const uint16_t* a, int as, const uint16_t* g, int gs, const ui
 void sums(const double* maps, int B, int HW, int runs, double* sum, hipStream_t s) {
   hipLaunchKernelGGL(k_sums, dim3(grid_for(HW, 32), B), dim3(256), 0, s, maps, HW, runs, sum);
 }
-void prep(const double* maps, const double* target, const double* sum, const int32_t* aug, int code_all, int B,
-          int H, int W, int runs, uint16_t* x, float* xq, float* ihat, float* tgt, hipStream_t s) {
-  hipLaunchKernelGGL(k_prep, dim3(grid_for((size_t)B * H * W)), dim3(256), 0, s, maps, target, sum, aug, code_all,
-                     B, H, W, runs, x, xq, ihat, tgt);
+void prep(const double* maps, const double* target, const double* sum, const int32_t* aug, int B, int H, int W,
+          int runs, uint16_t* x, float* xq, float* ihat, float* tgt, hipStream_t s) {
+  hipLaunchKernelGGL(k_prep, dim3(grid_for((size_t)B * H * W)), dim3(256), 0, s, maps, target, sum, aug, B,
+                     H, W, runs, x, xq, ihat, tgt);
 }
-void head(const uint16_t* d, int C, const float* hw, const float* hb, const float* xq, float* out, size_t P,
-          hipStream_t s) {
-  hipLaunchKernelGGL(k_head, dim3(grid_for(P * 8)), dim3(256), 0, s, d, C, hw, hb, xq, out, P);
+void turn(const uint16_t* x, int B, int H, int W, int code, uint16_t* y, hipStream_t s) {
+  hipLaunchKernelGGL(k_turn, dim3(grid_for((size_t)B * H * W)), dim3(256), 0, s, x, B, H, W, code, y);
+}
+void head(const uint16_t* d, int C, const float* hw, const float* hb, const float* xq, float* out, int B, int H, int W,
+          int code, bool first, hipStream_t s) {
+  const dim3 grid(grid_for((size_t)B * H * W * 8));
+  if (code < 0) hipLaunchKernelGGL(k_head<false>, grid, dim3(256), 0, s, d, C, hw, hb, xq, out, B, H, W, 0, 1);
+  else hipLaunchKernelGGL(k_head<true>, grid, dim3(256), 0, s, d, C, hw, hb, xq, out, B, H, W, code, (int)first);
 }
 void loss(const float* out, const float* tgt, const float* ihat, const double* sum, int B, int HW, float* go,
           double* l, hipStream_t s) {
@@ -478,10 +501,6 @@ void head_bwd(const float* go, const uint16_t* d, int C, const float* hw, float*
               size_t P, hipStream_t s) {
   hipLaunchKernelGGL(k_head_bwd, dim3((unsigned)((P + HB_CHUNK - 1) / HB_CHUNK)), dim3(256), 0, s, go, d, C, hw, ghw,
                      ghb, gd, P);
-}
-void tta_acc(const float* out, int B, int H, int W, int code, bool first, float* acc, hipStream_t s) {
-  hipLaunchKernelGGL(k_tta_acc, dim3(grid_for((size_t)B * H * W)), dim3(256), 0, s, out, B, H, W, code, (int)first,
-                     acc);
 }
 void output(const double* maps, const float* out, int B, int HW, int runs, double scale, double* dst,
             hipStream_t s) {

@@ -323,22 +323,29 @@ Low map_below(const kp_dn* dn, int l, size_t P) {
 }
 
 // maps -> w.out (network output: predicted fractions q', u'); activations kept
-// code_all >= 0: every image transformed by that dihedral element (test-time averaging)
+// code >= 0 (test-time averaging): one pass with every image transformed by that
+// dihedral element, its output added to w.go; passes start with code 0, whose
+// features the others turn (the gradient buffers are free in inference)
 kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, int H, int W, bool use_aug,
-                  hipStream_t s, int code_all = -1) {
+                  hipStream_t s, int code = -1) {
   Work& w = dn->w;
   const int L = dn->L;
   const int* c = dn->c;
-  const size_t P1 = (size_t)B * H * W;
   auto Hl = [&](int l) { return H >> l; };
   auto Wl = [&](int l) { return W >> l; };
   auto Pl = [&](int l) { return (size_t)B * (H >> l) * (W >> l); };
-  zero(w.sum, (size_t)B * 16, s);
-  sums(maps, B, H * W, dn->runs, w.sum, s);
-  prep(maps, target, w.sum, use_aug ? w.aug : nullptr, code_all, B, H, W, dn->runs, w.x0, w.xq, w.ihat, w.tgt, s);
+  const uint16_t* x0 = w.x0;
+  if (code <= 0) {
+    zero(w.sum, (size_t)B * 16, s);
+    sums(maps, B, H * W, dn->runs, w.sum, s);
+    prep(maps, target, w.sum, use_aug ? w.aug : nullptr, B, H, W, dn->runs, w.x0, w.xq, w.ihat, w.tgt, s);
+  } else {
+    turn(w.x0, B, H, W, code, w.gd[0], s);  // 8 of its at least 16 channels
+    x0 = w.gd[0];
+  }
   // encoder
   for (int l = 0; l < L - 1; ++l) {
-    const uint16_t* in = l == 0 ? w.x0 : w.pool[l];
+    const uint16_t* in = l == 0 ? x0 : w.pool[l];
     const int ins = l == 0 ? 8 : c[l - 1];
     conv_fwd(dn, dn->E(l), in, ins, w.ea[l], c[l], B, Hl(l), Wl(l), s);
     const bool means = conv_tiled(Pl(l));
@@ -367,7 +374,8 @@ kp_status forward(kp_dn* dn, const double* maps, const double* target, int B, in
     bs = c[l];
   }
   conv_done(dn, s);
-  head(w.dout[0], c[0], dn->d_p + dn->head_w, dn->d_p + dn->head_b, w.xq, w.out, P1, s);
+  head(w.dout[0], c[0], dn->d_p + dn->head_w, dn->d_p + dn->head_b, w.xq, code < 0 ? w.out : w.go, B, H, W, code,
+       code == 0, s);
   DN_HIP(hipGetLastError(), "denoiser forward launch");
   return KP_OK;
 }
@@ -669,11 +677,8 @@ kp_status kp_dn_infer_tta(kp_dn* dn, const double* d_maps, double* d_out, int32_
   if (kp_status st = ensure_packed(dn, s)) return st;
   // quarter turns need square images; otherwise the four elements without one
   const int step = H == W ? 1 : 2, n = 8 / step;
-  // the loss gradient buffer (unused by inference) accumulates the fractions
-  for (int code = 0; code < 8; code += step) {
+  for (int code = 0; code < 8; code += step)
     if (kp_status st = forward(dn, d_maps, nullptr, B, H, W, false, s, code)) return st;
-    tta_acc(dn->w.out, B, H, W, code, code == 0, dn->w.go, s);
-  }
   output(d_maps, dn->w.go, B, H * W, dn->runs, 1.0 / n, d_out, s);
   DN_HIP(hipGetLastError(), "output launch");
   if (dn->ev_total0 >= 0) {
