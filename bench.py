@@ -53,7 +53,7 @@ def counter_record():
     rec = json.load(open(path))
     csrc = os.path.join(ROOT, "paper_2512_01283_amd", "csrc")
     src = b"".join(open(os.path.join(csrc, f), "rb").read()
-                   for f in ("kp_kernels.hip", "kp_device.hpp", "kp_internal.hpp"))
+                   for f in ("kp_kernels.hip", "kp_device.hpp", "kp_internal.hpp", "kp_transfer.hpp"))
     if hashlib.sha256(src).hexdigest() != rec["source_sha256"]:
         return None
     return rec
