@@ -76,12 +76,8 @@ __device__ __forceinline__ void dichroic_cell(const DustDev& D, double b1, doubl
     Vn = st[3] * E + S[3] * tl * P;
   } else {
     // U + iV relaxes as exp(-(a1 - i a3) tau) toward the stationary state
-    const double x = -a1 * dtau, y = a3 * dtau;
-    const double ex = exp(x), cy = cos(y), sy = sin(y), sh = sin(0.5 * y);
-    const Cx<double> ez{ex * cy, ex * sy};
-    const Cx<double> em1{expm1(x) * cy - 2.0 * sh * sh, ex * sy};
-    const double den = x * x + y * y;
-    const Cx<double> phic{(em1.re * x + em1.im * y) / den, (em1.im * x - em1.re * y) / den};
+    Cx<double> ez, phic;
+    cx_exp_phi(-a1 * dtau, a3 * dtau, ez, phic);
     const Cx<double> Zn = cadd(cmul(Cx<double>{Ug, st[3]}, ez), cscale(cmul(Cx<double>{S2, S[3]}, phic), tl));
     Un = Zn.re;
     Vn = Zn.im;

@@ -916,12 +916,8 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
         Un = Ug * eU; Vn = p.V * eU;
       } else {
         // U + iV evolves as exp((-mU + i w) s)
-        const R x = -xU, y = (R)yd;
-        const R ex = k_exp(x), cy = k_cos(y), sy = k_sin(y), sh = k_sin((R)0.5 * y);
-        const Cx<R> ez{ex * cy, ex * sy};
-        const Cx<R> em1{k_expm1(x) * cy - (R)2 * sh * sh, ex * sy};
-        const R den = x * x + y * y;
-        const Cx<R> phic{(em1.re * x + em1.im * y) / den, (em1.im * x - em1.re * y) / den};
+        Cx<R> ez, phic;
+        cx_exp_phi(-xU, (R)yd, ez, phic);
         const Cx<R> Z{Ug, p.V};
         const Cx<R> JZ = cscale(cmul(Z, phic), tl), Zn = cmul(Z, ez);
         JUg = JZ.re; JVg = JZ.im; Un = Zn.re; Vn = Zn.im;

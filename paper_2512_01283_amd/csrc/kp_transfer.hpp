@@ -21,6 +21,19 @@ template <typename R> __device__ __forceinline__ Cx<R> cadd(Cx<R> a, Cx<R> b) {
 template <typename R> __device__ __forceinline__ R cabs2(Cx<R> a) { return a.re * a.re + a.im * a.im; }
 template <typename R> __device__ __forceinline__ Cx<R> cscale(Cx<R> a, R s) { return {a.re * s, a.im * s}; }
 
+// e^z and (e^z - 1) / z of z = x + i y.  Where |z|^2 would leave the type's normal
+// range (a ray through a cell's edge has no length in it; FP32 exponents of a
+// medium's thin wings) the quotient is its limit 1 + z / 2, whose next term z^2 / 6
+// is far below rounding there.
+template <typename R> __device__ __forceinline__ void cx_exp_phi(R x, R y, Cx<R>& ez, Cx<R>& phi) {
+  const R ex = k_exp(x), cy = k_cos(y), sy = k_sin(y), sh = k_sin((R)0.5 * y);
+  ez = {ex * cy, ex * sy};
+  const Cx<R> em1{k_expm1(x) * cy - (R)2 * sh * sh, ex * sy};
+  const R den = x * x + y * y;
+  if (den < (sizeof(R) == 4 ? (R)1e-30 : (R)1e-280)) phi = {(R)1 + (R)0.5 * x, (R)0.5 * y};
+  else phi = {(em1.re * x + em1.im * y) / den, (em1.im * x - em1.re * y) / den};
+}
+
 // Dimensionless extinction coefficients for a direction with cos(theta') =
 // ct to the grain axis (dipole: cross sections from Im of the
 // polarizability, normalised by the orientation average).
@@ -132,12 +145,8 @@ __device__ __forceinline__ void appA_eigen(double a1, double a2, double a3, doub
     Vn = s[3] * e + src[3] * g;
   } else {
     // U + iV relaxes as exp(-(a1 - i a3) tau) toward the stationary state
-    const double x = -a1 * dtau, y = a3 * dtau;
-    const double ex = exp(x), cy = cos(y), sy = sin(y), sh = sin(0.5 * y);
-    const Cx<double> ez{ex * cy, ex * sy};
-    const Cx<double> em1{expm1(x) * cy - 2.0 * sh * sh, ex * sy};
-    const double den = x * x + y * y;
-    const Cx<double> phic{(em1.re * x + em1.im * y) / den, (em1.im * x - em1.re * y) / den};
+    Cx<double> ez, phic;
+    cx_exp_phi(-a1 * dtau, a3 * dtau, ez, phic);
     const Cx<double> Z{s[2], s[3]}, SZ{src[2], src[3]};
     const Cx<double> Zn = cadd(cmul(Z, ez), cscale(cmul(SZ, phic), dtau));
     Un = Zn.re; Vn = Zn.im;
