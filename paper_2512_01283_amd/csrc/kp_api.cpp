@@ -253,15 +253,18 @@ void fill_dust(const kp_ctx* ctx, const uint64_t* counts, std::vector<DustDev>& 
       o.tab_g = 8 * (ctx->tab_nt - 1);
     }
     if (o.sphere) {
-      o.ap_re = o.aa_re = 1.0;
-      o.ap_im = o.aa_im = 0.0;
+      // only the modulus of a sphere's polarizability enters its scattering;
+      // with i the general kernels, which serve a sphere among dipole grains,
+      // form its extinction from the imaginary parts: alpha1 = 1, alpha2 = 0
+      o.ap_re = o.aa_re = 0.0;
+      o.ap_im = o.aa_im = 1.0;
     } else {
       o.ap_re = d.a_perp[0]; o.ap_im = d.a_perp[1];
       o.aa_re = d.a_par[0]; o.aa_im = d.a_par[1];
     }
     const double cavg = (2.0 * o.ap_im + o.aa_im) / 3.0;
-    o.inv2cavg = o.sphere ? 0.0 : 1.0 / (2.0 * cavg);
-    o.alpha3_scale = d.alpha3_scale;
+    o.inv2cavg = 1.0 / (2.0 * cavg);
+    o.alpha3_scale = o.sphere ? 0.0 : d.alpha3_scale;
     const double ap2 = o.ap_re * o.ap_re + o.ap_im * o.ap_im;
     const double aa2 = o.aa_re * o.aa_re + o.aa_im * o.aa_im;
     const double np = (2.0 * ap2 + aa2) / 3.0;
