@@ -238,13 +238,15 @@ __global__ void __launch_bounds__(256) k_image(ImageArgs a) {
     double clen = MESH ? ldexp(a.dx, -lvl) : a.dx;
     double inv_vol = 1.0 / (clen * clen * clen);
     // per axis: the face coordinate ahead, the step, the reciprocal direction
+    // (kept finite: that of a subnormal component overflows, and a ray that starts
+    // on the face ahead of it has no length left, not 0 times infinity)
     double face[3], rom[3];
     int stp[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       face[k] = om[k] > 0.0 ? 1.0 : 0.0;
       stp[k] = om[k] > 0.0 ? 1 : -1;
-      rom[k] = om[k] != 0.0 ? 1.0 / om[k] : 0.0;
+      rom[k] = om[k] != 0.0 ? fmin(1.7976931348623157e308, fmax(-1.7976931348623157e308, 1.0 / om[k])) : 0.0;
     }
     const double eBf = D.ka_cell / D.ke_cell;
     auto flat = [&]() {
