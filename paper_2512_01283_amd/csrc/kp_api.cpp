@@ -997,20 +997,27 @@ kp_status kp_transport(kp_ctx* ctx, const uint64_t* counts, const kp_opts* o, vo
   const bool all_sphere = all_spheres(ctx);
   const int ts = tally_stride(all_sphere);
   const uint64_t nslot = tally_layout(ctx).nslot;
-  size_t tally_need = (size_t)nl * nslot * cell_doubles(ctx);
+  const size_t tally_need = (size_t)nl * nslot * cell_doubles(ctx);
   int copies = hot_copies(ctx, total);
   const size_t trace_need = (size_t)nl * o->trace_packets;
   const size_t peel_need =
       o->peel_off ? (size_t)nl * ctx->views.size() * 4 * ctx->views[0].npx * ctx->views[0].npy : 0;
   size_t free_b = 0, total_b = 0;
   KP_HIP(hipMemGetInfo(&free_b, &total_b), "hipMemGetInfo");
-  if (copies && (tally_need + hot_doubles(ctx, copies)) * 8 > ctx->tally_n * 8 + free_b) copies = 0;
-  tally_need += hot_doubles(ctx, copies);
-  size_t extra = (tally_need > ctx->tally_n ? tally_need * 8 : 0) +
-                 (trace_need > ctx->traces_n ? trace_need * sizeof(TraceDev) : 0) +
-                 (peel_need > ctx->peel_n ? peel_need * 8 : 0);
+  const size_t other =
+      grow_bytes(trace_need, ctx->traces_n, sizeof(TraceDev)) + grow_bytes(peel_need, ctx->peel_n, sizeof(double));
+  copies = copies_that_fit(copies, tally_need, hot_doubles(ctx, 1), ctx->tally_n, other, free_b);
+  const size_t extra = grow_bytes(tally_need, ctx->tally_n, sizeof(double)) + other;
   if (extra > free_b) return fail(ctx, KP_ERR_OOM, "tally needs %zu bytes, %zu free", extra, free_b);
-  if ((st = ensure(ctx, &ctx->d_tally, &ctx->tally_n, tally_need, "tally allocation"))) return st;
+  // a tally that is replaced is gone, also if its successor cannot be allocated
+  if (tally_need + hot_doubles(ctx, copies) > ctx->tally_n) ctx->have_tally = false;
+  st = ensure(ctx, &ctx->d_tally, &ctx->tally_n, tally_need + hot_doubles(ctx, copies), "tally allocation");
+  if (st == KP_ERR_OOM && copies) {
+    (void)hipGetLastError();  // the failed allocation's, or the next launch check reports it
+    copies = 0;
+    st = ensure(ctx, &ctx->d_tally, &ctx->tally_n, tally_need, "tally allocation");
+  }
+  if (st) return st;
   if ((st = ensure(ctx, &ctx->d_traces, &ctx->traces_n, trace_need, "trace allocation"))) return st;
   if ((st = ensure(ctx, &ctx->d_peel, &ctx->peel_n, peel_need, "peel-off allocation"))) return st;
   ctx->peel_valid_n = 0;

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kp_rules.hpp"
+
 namespace kp {
 
 // Per-wavelength constants, prepared on the host from kp_dust.

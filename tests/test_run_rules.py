@@ -1,0 +1,61 @@
+"""The run's host-side decisions (csrc/kp_rules.hpp), compiled on their own."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_01283_amd", "csrc")
+
+
+def compiled(tmp, source):
+    src, lib = os.path.join(tmp, "rules.cpp"), os.path.join(tmp, "librules.so")
+    with open(src, "w") as f:
+        f.write('#include "kp_rules.hpp"\n' + source)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib],
+                   check=True)
+    return C.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    z = C.c_size_t
+    dll = compiled(str(tmp_path_factory.mktemp("rules")), """
+using namespace kp;
+extern "C" {
+int copies(int c, size_t tally, size_t per, size_t have, size_t other, size_t free_b) {
+  return copies_that_fit(c, tally, per, have, other, free_b);
+}
+size_t grow(size_t need, size_t have, size_t elem) { return grow_bytes(need, have, elem); }
+}
+""")
+    dll.copies.argtypes = [C.c_int, z, z, z, z, z]
+    dll.grow.argtypes, dll.grow.restype = [z, z, z], z
+    return dll
+
+
+def test_a_held_tally_is_not_refused_for_its_copies(lib):
+    """A context that holds the tally of a run below the copies' threshold, with
+    less free memory than another tally: nothing has to be allocated."""
+    assert lib.copies(8, 1000, 10, 1000, 0, 7999) == 0
+    assert lib.copies(8, 1000, 10, 1000, 0, 8 * 1080 - 1) == 0
+    assert lib.copies(8, 1000, 10, 1000, 0, 8 * 1080) == 8
+    assert lib.copies(8, 1000, 10, 1080, 0, 0) == 8  # room is left in the buffer
+    assert lib.copies(0, 1000, 10, 1000, 0, 0) == 0
+
+
+def test_copies_never_refuse_a_run(lib):
+    """Whatever is held and free, a run that fits without copies fits with those it gets."""
+    n = 0
+    for tally in (0, 5, 64, 100):
+        for have in (0, 4, 64, 100, 120, 400):
+            for other in (0, 8, 200):
+                for free in range(0, 2200, 13):
+                    for want in (0, 2, 32):
+                        if lib.grow(tally, have, 8) + other > free:
+                            continue
+                        got = lib.copies(want, tally, 7, have, other, free)
+                        assert got in (0, want)
+                        assert lib.grow(tally + 7 * got, have, 8) + other <= free
+                        n += got > 0
+    assert n > 1000
