@@ -564,7 +564,7 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   a.tbx = tl.tbx;
   a.tby = tl.tby;
   a.hot_copies = b.hot_copies;
-  a.hot_x = a.hot_y = a.hot_z = INT32_MIN;
+  a.hot_x = a.hot_y = a.hot_z = HOT_NONE;
   if (b.hot_copies) {
     const kp_grid& g = ctx->grid;
     a.hot_x = (int)std::floor((ctx->src.pos[0] - g.x0) / g.dx) - HOT_SIDE / 2;

@@ -84,20 +84,6 @@ struct MeshDev {
 // refused
 constexpr int KP_MAX_STEPS = 1 << 24;
 
-// Near a point source every packet adds to the same few cells, and the L2 takes
-// one addition to a line about every 37 ns: 1e6 packets leaving a grid vertex
-// spend 4.6 ms on the eight cells around it.  The cells of an 8 x 8 x 8 box around
-// the source (HOT_SIDE^3) are therefore tallied in HOT_COPIES copies behind the
-// tally, one per group of wavefronts, and summed into it after the launch
-// (k_hot_sum).  Transport: aligned slab, 3e6 packets 33.3 -> 17.7 ms; 45^3 disk,
-// 1.9e6: 8.9 -> 2.7; 100^3 sphere, 3e6: 20.4 -> 15.6 (its 2.4e10 lines/s are the
-// L2's limit); the 256^3 disk, whose hole surrounds the star, +1 %.
-constexpr int HOT_SIDE = 8;
-constexpr int HOT_CELLS = HOT_SIDE * HOT_SIDE * HOT_SIDE;
-constexpr int HOT_COPIES = 32;                    // at most
-constexpr size_t HOT_BYTES = size_t(16) << 20;    // of all copies and wavelengths together
-constexpr uint64_t HOT_MIN_PACKETS = 1u << 15;    // fewer packets queue for less than the sum costs
-
 // LDS (doubles per block) that tabulated grains' tables may take with two
 // blocks of their kernel on a CU: one wavelength of 361 nodes and 16 cameras, or
 // two of 181
@@ -126,7 +112,7 @@ struct TransportArgs {
   uint64_t nslot;  // tally slots per wavelength (tally_slots; ncell on a mesh)
   int tbx, tby;    // bricks along x and y of the tally layout (0 on a mesh)
   int hot_x, hot_y, hot_z;  // lowest cell of the box of copied cells
-  int hot_copies;           // copies of it behind the tally (0: none, hot_x = INT32_MIN)
+  int hot_copies;           // copies of it behind the tally (0: none, hot_x = HOT_NONE)
   unsigned long long* counter;
   StatsDev* stats;
   TraceDev* traces;

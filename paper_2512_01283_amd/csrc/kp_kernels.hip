@@ -947,7 +947,7 @@ __device__ uint32_t step(Packet<R>& p, const ColdRef& kc, const TransportArgs& a
       uint64_t slot = (uint64_t)p.lam * a.nslot + sl;
       if (!MESH) {
         // a cell of the box around the source: this wavefront's copy of it
-        const uint32_t hx = (uint32_t)(ci0 - a.hot_x), hy = (uint32_t)(cj0 - a.hot_y), hz = (uint32_t)(ck0 - a.hot_z);
+        const uint32_t hx = hot_index(ci0, a.hot_x), hy = hot_index(cj0, a.hot_y), hz = hot_index(ck0, a.hot_z);
         if ((hx | hy | hz) < (uint32_t)HOT_SIDE)
           slot = hot_base + (uint64_t)((uint32_t)p.lam * HOT_CELLS + (hx + HOT_SIDE * (hy + HOT_SIDE * hz)));
       }

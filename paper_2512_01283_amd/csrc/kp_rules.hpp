@@ -10,6 +10,26 @@ namespace kp {
 // `need`: nothing, or, as it is replaced, all of the new one.
 constexpr size_t grow_bytes(size_t need, size_t have, size_t elem) { return need > have ? need * elem : 0; }
 
+// Near a point source every packet adds to the same few cells, and the L2 takes
+// one addition to a line about every 37 ns: 1e6 packets leaving a grid vertex
+// spend 4.6 ms on the eight cells around it.  The cells of an 8 x 8 x 8 box around
+// the source (HOT_SIDE^3) are therefore tallied in HOT_COPIES copies behind the
+// tally, one per group of wavefronts, and summed into it after the launch
+// (k_hot_sum).  Transport: aligned slab, 3e6 packets 33.3 -> 17.7 ms; 45^3 disk,
+// 1.9e6: 8.9 -> 2.7; 100^3 sphere, 3e6: 20.4 -> 15.6 (its 2.4e10 lines/s are the
+// L2's limit); the 256^3 disk, whose hole surrounds the star, +1 %.
+constexpr int HOT_SIDE = 8;
+constexpr int HOT_CELLS = HOT_SIDE * HOT_SIDE * HOT_SIDE;
+constexpr int HOT_COPIES = 32;                    // at most
+constexpr size_t HOT_BYTES = size_t(16) << 20;    // of all copies and wavelengths together
+constexpr uint64_t HOT_MIN_PACKETS = 1u << 15;    // fewer packets queue for less than the sum costs
+
+// a cell's index along one axis of the box whose lowest cell is `low`; HOT_SIDE or
+// more outside it, and for every cell where low is HOT_NONE (in unsigned numbers:
+// the signed difference would overflow there)
+constexpr int HOT_NONE = INT32_MIN;
+constexpr uint32_t hot_index(int cell, int low) { return (uint32_t)cell - (uint32_t)low; }
+
 // Copies of the cells around the source (HOT_COPIES) that a run takes: those it
 // wants, or none where the tally of `tally` doubles would fit but not with
 // `per_copy` more for each.  have: doubles allocated; other: bytes that the

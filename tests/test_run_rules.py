@@ -59,3 +59,23 @@ def test_copies_never_refuse_a_run(lib):
                         assert lib.grow(tally + 7 * got, have, 8) + other <= free
                         n += got > 0
     assert n > 1000
+
+
+def test_the_copied_box_without_overflow(tmp_path):
+    """Every cell against boxes inside, across and outside the grid, and against
+    none, in constant expressions: the compiler refuses one that overflows."""
+    compiled(str(tmp_path), """
+#include <initializer_list>
+using namespace kp;
+constexpr bool in(int cell, int low) { return hot_index(cell, low) < (uint32_t)HOT_SIDE; }
+constexpr bool all(int n) {
+  for (int c = 0; c < n; ++c) {
+    if (in(c, HOT_NONE)) return false;
+    for (int low : {-HOT_SIDE, -HOT_SIDE + 1, -1, 0, 1, 17, n - 1, n})
+      if (in(c, low) != (c >= low && c < low + HOT_SIDE)) return false;
+  }
+  return true;
+}
+static_assert(all(40));
+static_assert(!in(2147483647, HOT_NONE) && in(2147483647, 2147483640));
+""")
