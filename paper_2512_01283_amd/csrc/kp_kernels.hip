@@ -432,7 +432,7 @@ __device__ __forceinline__ int wave_stage_new(bool need, int64_t key, const doub
   return n;
 }
 template <int NC, typename R>
-__device__ __forceinline__ int wave_stage(bool has, int64_t key, const R cc[NC], double* sv, long long* sk, int lane,
+__device__ __forceinline__ void wave_stage(bool has, int64_t key, const R cc[NC], double* sv, long long* sk, int lane,
                                           int& staged, int64_t& last_key, int& slot) {
   const bool same = has && slot >= 0 && key == last_key;
   if (same) {
@@ -443,13 +443,13 @@ __device__ __forceinline__ int wave_stage(bool has, int64_t key, const R cc[NC],
 #pragma unroll
   for (int k = 0; k < NC; ++k) v[k] = (double)cc[k];
   if (has) last_key = key;
-  return wave_stage_new<NC>(has && !same, key, v, sv, sk, lane, staged, slot);
+  wave_stage_new<NC>(has && !same, key, v, sv, sk, lane, staged, slot);
 }
 
 template <int NC, int TS>
-__device__ __forceinline__ void wave_drain(double* tally, double* sv, long long* sk, int lane, int& staged) {
+__device__ __forceinline__ int wave_drain(double* tally, double* sv, long long* sk, int lane, int& staged) {
   const int n = staged;
-  if (n == 0) return;
+  if (n == 0) return 0;
   staged = 0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -482,6 +482,60 @@ __device__ __forceinline__ void wave_drain(double* tally, double* sv, long long*
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return n;
+}
+
+// The same for the packets of a pencil beam, which all cross the same cells, those
+// that started together at the same time: each group of NC lanes takes a run
+// of consecutive entries and adds those of one cell up before they go to memory.
+// The beam's lines are otherwise what bounds such a run, the more so the more
+// wavefronts contend for them: 64-cell column, 3e5 packets, 5.4, 6.3 and 7.2 ms
+// with one, two and three blocks per CU, so 0.85 ms; a beam across a 64^3 sphere of
+// depth 1, where most entries are scattered light's, 5.8 -> 3.5, of depth 20 21.6.
+// Returns the blocks added.
+template <int NC, int TS>
+__device__ __forceinline__ int wave_drain_runs(double* tally, const double* sv, const long long* sk, int lane,
+                                               int& staged) {
+  const int n = staged;
+  if (n == 0) return 0;
+  staged = 0;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  constexpr int G = 64 / NC;
+  constexpr int U = 4;  // entries whose LDS reads are issued before one wait
+  const int slot = lane / NC, k = lane - slot * NC, per = (n + G - 1) / G;
+  const int end = slot < G ? min(n, (slot + 1) * per) : 0;
+  int blocks = 0;
+  long long cur = -1;
+  double sum = 0.0;
+  for (int i = 0; i < per; i += U) {
+    double v[U];
+    long long key[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = min(slot * per + i + u, n - 1);
+      v[u] = sv[e * NC + (slot < G ? k : 0)];
+      key[u] = sk[e];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool have = i + u < per && slot * per + i + u < end;
+      const bool out = have && key[u] != cur && cur >= 0;
+      blocks += __popcll(__ballot(out && k == 0));
+      if (out && sum != 0.0) unsafeAtomicAdd(tally + (uint64_t)cur * TS + k, sum);
+      if (have) {
+        sum = key[u] == cur ? sum + v[u] : v[u];
+        cur = key[u];
+      }
+    }
+  }
+  blocks += __popcll(__ballot(cur >= 0 && k == 0));
+  if (cur >= 0 && sum != 0.0) unsafeAtomicAdd(tally + (uint64_t)cur * TS + k, sum);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return blocks;
 }
 
 // Spherical grains' scattering in real arithmetic: the Jones matrix J_ij =
@@ -1443,6 +1497,11 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   // condition of two keeps 30 more registers alive)
   int refill_at = lanes - max(1, REFILL_BATCH * lanes >> 6);
   bool global_done = false;  // the global counter has passed the total
+  auto drain = [&]() {
+    const TransportArgs r = reload_args(staged);
+    return r.src_kind == 1 ? wave_drain_runs<NC, TS>(r.tally, sv, sk, lane, staged)
+                           : wave_drain<NC, TS>(r.tally, sv, sk, lane, staged);
+  };
   uint32_t ended = 0;        // this lane's packet has ended (its end kind), not yet reported
   while (true) {
     // Ended packets are reported (finish) and their lanes refilled for
@@ -1516,9 +1575,9 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
         else wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
       }
     } else {
-      flushes += wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
+      wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
       if (staged > FLUSH_CAP - 64) {
-        wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
+        flushes += drain();
         slot = -1;
       }
     }
@@ -1546,7 +1605,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   }
   if (TAB && a.tab_lds) wave_drain_views<MESH, true>(a, sv, sk, sp, sa, s_tab, lane, staged);
   else if (TAB) wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
-  else wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
+  else flushes += drain();
   if (lane == 0) atomicAdd(&sc[SC_FLUSH], flushes);
   __syncthreads();
   if (threadIdx.x < SC_N) atomicAdd(&(&a.stats->cell_steps)[threadIdx.x], sc[threadIdx.x]);
