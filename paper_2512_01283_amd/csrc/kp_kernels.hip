@@ -1589,8 +1589,7 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
     if (pm) {
       ++waited;
       const unsigned long long movable = __ballot(active && !ended && !pending);
-      // (with no packets left to take, a share of those still under way)
-      const int batch = exhausted ? a.scatter_batch * nactive >> 6 : a.scatter_batch * lanes >> 6;
+      const int batch = events_together(a.scatter_batch, lanes, nactive, exhausted, PEEL);
       if (__popcll(pm) >= batch || waited >= a.scatter_wait || movable == 0ull) {
         waited = 0;
         if (pending) {

@@ -40,4 +40,14 @@ constexpr int copies_that_fit(int copies, size_t tally, size_t per_copy, size_t 
   return grow_bytes(tally + (size_t)copies * per_copy, have, sizeof(double)) + other <= free_b ? copies : 0;
 }
 
+// Parked lanes from which a wavefront of `lanes` packets (`nactive` still under way,
+// no ids left if `exhausted`) runs their scattering events together: that share of
+// a full wavefront's setting.  With peel-off an event marches to every camera,
+// once for all the lanes that run it together, and the setting stays as it is:
+// aligned grains in a 32^3 sphere, one camera, 3e4 packets 2.9 ms, 4.7 with the
+// share; 8 cameras, 17 and 38 ms; spheres, 3e4 packets, 1.6 and 2.7 ms.
+constexpr int events_together(int batch, int lanes, int nactive, bool exhausted, bool peel) {
+  return peel ? batch : batch * (exhausted ? nactive : lanes) >> 6;
+}
+
 }  // namespace kp

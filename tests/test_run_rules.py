@@ -26,6 +26,9 @@ extern "C" {
 int copies(int c, size_t tally, size_t per, size_t have, size_t other, size_t free_b) {
   return copies_that_fit(c, tally, per, have, other, free_b);
 }
+int events(int batch, int lanes, int nactive, int exhausted, int peel) {
+  return events_together(batch, lanes, nactive, exhausted, peel);
+}
 size_t grow(size_t need, size_t have, size_t elem) { return grow_bytes(need, have, elem); }
 }
 """)
@@ -79,3 +82,15 @@ constexpr bool all(int n) {
 static_assert(all(40));
 static_assert(!in(2147483647, HOT_NONE) && in(2147483647, 2147483640));
 """)
+
+
+def test_scattering_events_together(lib):
+    """The setting's share of the lanes in use, or of the packets left; with
+    peel-off, whose events cost far more than the steps meanwhile, the setting."""
+    for batch in (1, 8, 64):
+        assert lib.events(batch, 64, 64, 0, 0) == batch
+        for lanes in (1, 29, 64):
+            for nactive in range(1, lanes + 1):
+                assert lib.events(batch, lanes, nactive, 0, 0) == batch * lanes // 64
+                assert lib.events(batch, lanes, nactive, 1, 0) == batch * nactive // 64
+                assert lib.events(batch, lanes, nactive, 0, 1) == lib.events(batch, lanes, nactive, 1, 1) == batch
