@@ -1,5 +1,7 @@
 // kp_image.hip -- gfx950 kernels of the deterministic imaging ray-march (step
 // 2) of Yang & Wang, arXiv:2512.01283, Sec. 2.3 and Appendix A.
+#include <type_traits>
+
 #include "kp_transfer.hpp"
 
 namespace kp {
@@ -124,9 +126,12 @@ __device__ __forceinline__ void dipole_source(const double C9[9], const Camera& 
 // extinction for the camera direction and the scattering source formed from
 // the coherency tally (or a caller-given per-view source).  FP64 throughout.
 // A wavefront takes 8 x 8 pixels and a 256-thread block 16 x 16, so that rays
-// marching together cross the same cells' lines; consecutive blocks, which the
-// hardware deals out over the 8 XCDs, are regrouped so that one XCD's L2 serves
-// neighbouring tiles.  A cell costs six numbers against the camera's constants
+// marching together cross the same cells' lines; a map that is no multiple of them
+// is packed without gaps (image_pixel), small ones share wavefronts (MULTI):
+// padded to 16 x 16, images of 17 x 17 pixels took 1.8 ms instead of 0.6 (64^3 sphere,
+// 64 views, 32 wavelengths), of 4096 x 1 with 8 views 414 us instead of 90.  Consecutive
+// blocks, which the hardware deals out over the 8 XCDs, are regrouped so that one XCD's
+// L2 serves neighbouring tiles.  A cell costs six numbers against the camera's constants
 // (spheres) or three products with its grain axis (dichroic grains), one
 // exponential per eigenvalue and no division by the density; what then bounds
 // a large grid are the L2's misses on the tally's 64-byte sectors (50 G/s: little of
@@ -142,28 +147,33 @@ __device__ __forceinline__ void dipole_source(const double C9[9], const Camera& 
 // early (a two-cell pipeline) measured 2.3 ms and 6.4 ms: it adds lines in flight, and
 // it is their reuse that is short.
 // ---------------------------------------------------------------------------
-template <bool ALIGNED, bool SPHERE, bool USER_S, bool MESH>
+template <bool ALIGNED, bool SPHERE, bool USER_S, bool MESH, bool MULTI>
 __global__ void __launch_bounds__(256) k_image(ImageArgs a) {
   // No fused multiply-adds in the geometry: a ray that grazes a cell face (a
   // pixel centre on a face, drifting off it by ~1e-16 per cell) then takes the
   // face-side decisions of a plain (unfused) evaluation of the same expressions.
 #pragma clang fp contract(off)
   static_assert(!(ALIGNED && SPHERE), "the extinction of spheres is scalar");
-  const uint32_t txn = (uint32_t)(a.npx + 15) >> 4, tyn = (uint32_t)(a.npy + 15) >> 4;
-  const uint32_t nsub = 4u * txn * tyn;  // wavefronts per (wavelength, view)
+  const uint64_t npix = (uint64_t)a.npx * a.npy;
   uint32_t blk = blockIdx.x;
   if (blk < gridDim.x - gridDim.x % 8u) blk = (blk & 7u) * (gridDim.x / 8u) + (blk >> 3);
   const uint32_t wave =
       (uint32_t)__builtin_amdgcn_readfirstlane((int)(blk * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-  const uint32_t map = wave / nsub, sub = wave - map * nsub;
+  // the (wavelength, view) map of this lane's pixel and the pixel's place in it
+  uint32_t map, px = threadIdx.x & 63u;
+  if (MULTI) {
+    px += 64u * wave;
+    map = px / (uint32_t)npix;
+    px -= map * (uint32_t)npix;
+  } else {
+    const uint32_t per = ((uint32_t)npix + 63u) >> 6;
+    map = wave / per;
+    px += 64u * (wave - map * per);
+  }
   const int lam = (int)(map / (uint32_t)a.n_views), v = (int)(map - (uint32_t)lam * (uint32_t)a.n_views);
-  if (lam >= a.n_lambda) return;
-  const int lane = (int)(threadIdx.x & 63u);
-  const uint32_t tile = sub >> 2, ty = tile / txn;
-  const int ix = (int)((tile - ty * txn) * 16u + (sub & 1u) * 8u) + (lane & 7);
-  const int iy = (int)(ty * 16u + ((sub >> 1) & 1u) * 8u) + (lane >> 3);
-  if (ix >= a.npx || iy >= a.npy) return;
-  const uint64_t npix = (uint64_t)a.npx * a.npy;
+  if (lam >= a.n_lambda || px >= npix) return;
+  int ix, iy;
+  image_pixel(px, (uint32_t)a.npx, (uint32_t)a.npy, ix, iy);
   const ViewDev vw = a.views[v];
   const DustDev& D = a.dust[lam];
   const double W = vw.half_width;
@@ -354,30 +364,37 @@ __global__ void __launch_bounds__(256) k_image(ImageArgs a) {
   for (int k = 0; k < 4; ++k) out[(uint64_t)k * npix] = st[k];
 }
 
-template <bool U, bool M>
+template <bool U, bool M, bool X>
 static void launch_image_one(const ImageArgs& a, bool aligned, bool sphere, dim3 grid, int bs, hipStream_t s) {
   // On a uniform grid spheres' registers would let four blocks run per CU;
   // their rays then cross 4 MB of the tally per step on each XCD, all of its L2, and a
   // line is gone before the neighbouring rays reach it.  Half a CU's LDS, not
   // used, keeps it at two blocks: 256^3 disk 2.62 (four), 2.28 (three), 1.94 ms
   // (two), 2.40 (one); grids that fit the L2s measured the same either way.
-  const size_t lds = sphere && !U && !M && bs == 256 ? size_t(80) << 10 : 0;
-  if (sphere) hipLaunchKernelGGL((k_image<false, true, U, M>), grid, dim3(bs), lds, s, a);
-  else if (aligned) hipLaunchKernelGGL((k_image<true, false, U, M>), grid, dim3(bs), 0, s, a);
-  else hipLaunchKernelGGL((k_image<false, false, U, M>), grid, dim3(bs), 0, s, a);
+  const size_t lds = sphere && !U && !M && !X && bs == 256 ? size_t(80) << 10 : 0;
+  if (sphere) hipLaunchKernelGGL((k_image<false, true, U, M, X>), grid, dim3(bs), lds, s, a);
+  else if (aligned) hipLaunchKernelGGL((k_image<true, false, U, M, X>), grid, dim3(bs), 0, s, a);
+  else hipLaunchKernelGGL((k_image<false, false, U, M, X>), grid, dim3(bs), 0, s, a);
 }
 
 hipError_t launch_image(const ImageArgs& a, bool aligned, bool sphere, bool user_source, bool mesh, hipStream_t s) {
-  const uint64_t waves = (uint64_t)((a.npx + 15) / 16) * ((a.npy + 15) / 16) * 4 * a.n_views * a.n_lambda;
+  const uint64_t npix = (uint64_t)a.npx * a.npy, maps = (uint64_t)a.n_views * a.n_lambda;
+  const bool multi = image_multi(npix);
+  const uint64_t waves = image_waves(npix, maps);
   // few wavefronts go one to a block, so that they spread over the CUs
   const int bs = waves < 1024 ? 64 : 256;
   const uint64_t blocks = (waves * 64 + bs - 1) / bs;
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
-  if (user_source && mesh) launch_image_one<true, true>(a, aligned, sphere, grid, bs, s);
-  else if (user_source) launch_image_one<true, false>(a, aligned, sphere, grid, bs, s);
-  else if (mesh) launch_image_one<false, true>(a, aligned, sphere, grid, bs, s);
-  else launch_image_one<false, false>(a, aligned, sphere, grid, bs, s);
+  auto go = [&](auto x) {
+    constexpr bool X = decltype(x)::value;
+    if (user_source && mesh) launch_image_one<true, true, X>(a, aligned, sphere, grid, bs, s);
+    else if (user_source) launch_image_one<true, false, X>(a, aligned, sphere, grid, bs, s);
+    else if (mesh) launch_image_one<false, true, X>(a, aligned, sphere, grid, bs, s);
+    else launch_image_one<false, false, X>(a, aligned, sphere, grid, bs, s);
+  };
+  if (multi) go(std::true_type{});
+  else go(std::false_type{});
   return hipGetLastError();
 }
 

@@ -50,4 +50,37 @@ constexpr int events_together(int batch, int lanes, int nactive, bool exhausted,
   return peel ? batch : batch * (exhausted ? nactive : lanes) >> 6;
 }
 
+// Pixel p of an npx x npy image in the order that the imaging wavefronts take them:
+// bands of 16 rows, in them groups of 16 columns, in them 8 rows and 8 columns at a
+// time, each row by row.  64 consecutive pixels are an 8 x 8 tile and 256 a 16 x 16
+// one where the image has room for them, and no pixel is missing where not.
+constexpr void image_pixel(uint32_t p, uint32_t npx, uint32_t npy, int& ix, int& iy) {
+  const uint32_t band = p / (16u * npx);
+  p -= band * 16u * npx;
+  const uint32_t h = npy - 16u * band < 16u ? npy - 16u * band : 16u;
+  const uint32_t group = p / (16u * h);
+  p -= group * 16u * h;
+  const uint32_t w = npx - 16u * group < 16u ? npx - 16u * group : 16u;
+  const uint32_t row = p / (8u * w);
+  p -= row * 8u * w;
+  const uint32_t h8 = h - 8u * row < 8u ? h - 8u * row : 8u;
+  const uint32_t col = p / (8u * h8);
+  p -= col * 8u * h8;
+  const uint32_t w8 = w - 8u * col < 8u ? w - 8u * col : 8u;
+  iy = (int)(16u * band + 8u * row + p / w8);
+  ix = (int)(16u * group + 8u * col + p % w8);
+}
+
+// A wavefront takes 64 pixels of one (wavelength, view) map, so that its camera and
+// grain constants are scalars; where a map leaves more than 0.3 of its wavefronts'
+// lanes without a pixel, it takes 64 pixels of any maps.  64^3 sphere / aligned
+// grains, one map's pixels and any (us): 256 views x 32 wavelengths of 4 x 4 pixels
+// 435 / 994 and 193 / 465, of 5 x 5 474 / 1015 and 322 / 832, of 9 x 9 859 / 1825 and
+// 676 / 1809, of 8 x 8 591 / 1308 and 562 / 1490; 64 x 32 of 12 x 12 400 / 899 and 408 /
+// 1015.
+constexpr bool image_multi(uint64_t npix) { return 10u * npix < 7u * ((npix + 63u) / 64u * 64u); }
+constexpr uint64_t image_waves(uint64_t npix, uint64_t maps) {
+  return image_multi(npix) ? (maps * npix + 63u) / 64u : maps * ((npix + 63u) / 64u);
+}
+
 }  // namespace kp

@@ -3,6 +3,7 @@ import ctypes as C
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_01283_amd", "csrc")
@@ -29,10 +30,15 @@ int copies(int c, size_t tally, size_t per, size_t have, size_t other, size_t fr
 int events(int batch, int lanes, int nactive, int exhausted, int peel) {
   return events_together(batch, lanes, nactive, exhausted, peel);
 }
+void pixels(unsigned npx, unsigned npy, int* xy) {
+  for (unsigned p = 0; p < npx * npy; ++p) image_pixel(p, npx, npy, xy[2 * p], xy[2 * p + 1]);
+}
+size_t waves(size_t npix, size_t maps) { return (size_t)image_waves(npix, maps); }
 size_t grow(size_t need, size_t have, size_t elem) { return grow_bytes(need, have, elem); }
 }
 """)
     dll.copies.argtypes = [C.c_int, z, z, z, z, z]
+    dll.waves.argtypes, dll.waves.restype = [z, z], z
     dll.grow.argtypes, dll.grow.restype = [z, z, z], z
     return dll
 
@@ -94,3 +100,33 @@ def test_scattering_events_together(lib):
                 assert lib.events(batch, lanes, nactive, 0, 0) == batch * lanes // 64
                 assert lib.events(batch, lanes, nactive, 1, 0) == batch * nactive // 64
                 assert lib.events(batch, lanes, nactive, 0, 1) == lib.events(batch, lanes, nactive, 1, 1) == batch
+
+
+def pixels(lib, npx, npy):
+    xy = np.full((npx * npy, 2), -1, np.int32)
+    lib.pixels(npx, npy, xy.ctypes.data_as(C.c_void_p))
+    return xy
+
+
+@pytest.mark.parametrize("npx,npy", [(1, 1), (1, 300), (300, 1), (2, 3), (7, 9), (8, 8), (16, 16), (17, 17), (15, 33),
+                                     (33, 15), (70, 3), (3, 70), (64, 64), (100, 172), (16384, 2), (1, 16384)])
+def test_image_order_takes_every_pixel_once(lib, npx, npy):
+    xy = pixels(lib, npx, npy)
+    assert xy.min() >= 0 and xy[:, 0].max() == npx - 1 and xy[:, 1].max() == npy - 1
+    assert np.array_equal(np.sort(xy[:, 0] + npx * xy[:, 1]), np.arange(npx * npy))
+
+
+def test_image_order_of_whole_tiles(lib):
+    xy = pixels(lib, 48, 32)
+    for size, side in ((64, 8), (256, 16)):
+        for t in xy.reshape(-1, size, 2):
+            assert (t.max(0) - t.min(0) == side - 1).all() and (t.min(0) % side == 0).all()
+
+
+def test_image_wavefronts_have_pixels(lib):
+    """No image shape leaves more than 0.3 of its wavefronts' lanes idle."""
+    for npix in [*range(1, 700), 17 * 17, 3 * 70, 16384, 100 * 172]:
+        for maps in (1, 7, 64, 4096):
+            waves = lib.waves(npix, maps)
+            assert 64 * waves >= npix * maps
+            assert 0.7 * 64 * (waves - 1) <= npix * maps, (npix, maps)
