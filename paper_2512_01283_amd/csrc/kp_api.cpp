@@ -605,7 +605,8 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   const int bs = o->block_size ? o->block_size : 256;
   int bpc = o->blocks_per_cu;
   if (bpc == 0) {
-    bpc = transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, bs, a.tab_lds);
+    bpc = transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, a.src_kind, bs,
+                                      a.tab_lds);
     if (bpc < 1) bpc = 1;
     if (bpc > 8) bpc = 8;
   }

@@ -202,7 +202,7 @@ hipError_t launch_validate(const float* rho, const float* bx, const float* by, c
 // (ts doubles per cell slot, the first nc of them sums)
 hipError_t launch_hot_sum(const TransportArgs& a, int ts, int nc, hipStream_t s);
 int transport_max_blocks_per_cu(bool fp64, bool aligned, bool sphere, bool peel, bool tab, bool mesh,
-                                int block_size, int tab_lds);
+                                int src_kind, int block_size, int tab_lds);
 // Thermal emission tables of one wavelength: cdf [ncell], the running sum
 // of fac rho B (fac = 4 pi kappa_abs dx^3; on a composite mesh, leaf_org
 // non-null, times 2^-3 level of each cell's leaf, block3 cells per leaf) in

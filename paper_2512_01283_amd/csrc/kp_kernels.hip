@@ -432,7 +432,7 @@ __device__ __forceinline__ int wave_stage_new(bool need, int64_t key, const doub
   return n;
 }
 template <int NC, typename R>
-__device__ __forceinline__ void wave_stage(bool has, int64_t key, const R cc[NC], double* sv, long long* sk, int lane,
+__device__ __forceinline__ int wave_stage(bool has, int64_t key, const R cc[NC], double* sv, long long* sk, int lane,
                                           int& staged, int64_t& last_key, int& slot) {
   const bool same = has && slot >= 0 && key == last_key;
   if (same) {
@@ -443,13 +443,13 @@ __device__ __forceinline__ void wave_stage(bool has, int64_t key, const R cc[NC]
 #pragma unroll
   for (int k = 0; k < NC; ++k) v[k] = (double)cc[k];
   if (has) last_key = key;
-  wave_stage_new<NC>(has && !same, key, v, sv, sk, lane, staged, slot);
+  return wave_stage_new<NC>(has && !same, key, v, sv, sk, lane, staged, slot);
 }
 
 template <int NC, int TS>
-__device__ __forceinline__ int wave_drain(double* tally, double* sv, long long* sk, int lane, int& staged) {
+__device__ __forceinline__ void wave_drain(double* tally, double* sv, long long* sk, int lane, int& staged) {
   const int n = staged;
-  if (n == 0) return 0;
+  if (n == 0) return;
   staged = 0;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -482,7 +482,6 @@ __device__ __forceinline__ int wave_drain(double* tally, double* sv, long long* 
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  return n;
 }
 
 // The same for the packets of a pencil beam, which all cross the same cells, those
@@ -1412,7 +1411,7 @@ __device__ __forceinline__ TransportArgs reload_args(int varying) {
   return r;
 }
 
-template <typename R, bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
+template <typename R, bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH, bool BEAM>
 __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   constexpr int NC = TallyShape<SPHERE>::NC, TS = TallyShape<SPHERE>::TS;
   __shared__ unsigned long long sc[SC_N];
@@ -1497,11 +1496,6 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   // condition of two keeps 30 more registers alive)
   int refill_at = lanes - max(1, REFILL_BATCH * lanes >> 6);
   bool global_done = false;  // the global counter has passed the total
-  auto drain = [&]() {
-    const TransportArgs r = reload_args(staged);
-    return r.src_kind == 1 ? wave_drain_runs<NC, TS>(r.tally, sv, sk, lane, staged)
-                           : wave_drain<NC, TS>(r.tally, sv, sk, lane, staged);
-  };
   uint32_t ended = 0;        // this lane's packet has ended (its end kind), not yet reported
   while (true) {
     // Ended packets are reported (finish) and their lanes refilled for
@@ -1575,9 +1569,11 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
         else wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
       }
     } else {
-      wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
+      const int added = wave_stage<NC, R>(has, key, cc, sv, sk, lane, staged, last_key, slot);
+      if (!BEAM) flushes += added;
       if (staged > FLUSH_CAP - 64) {
-        flushes += drain();
+        if (BEAM) flushes += wave_drain_runs<NC, TS>(a.tally, sv, sk, lane, staged);
+        else wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
         slot = -1;
       }
     }
@@ -1604,7 +1600,8 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   }
   if (TAB && a.tab_lds) wave_drain_views<MESH, true>(a, sv, sk, sp, sa, s_tab, lane, staged);
   else if (TAB) wave_drain_views<MESH, false>(a, sv, sk, sp, sa, s_tab, lane, staged);
-  else flushes += drain();
+  else if (BEAM) flushes += wave_drain_runs<NC, TS>(a.tally, sv, sk, lane, staged);
+  else wave_drain<NC, TS>(a.tally, sv, sk, lane, staged);
   if (lane == 0) atomicAdd(&sc[SC_FLUSH], flushes);
   __syncthreads();
   if (threadIdx.x < SC_N) atomicAdd(&(&a.stats->cell_steps)[threadIdx.x], sc[threadIdx.x]);
@@ -1627,15 +1624,15 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
 // registers at four waves: 15.5 ms).  PEEL adds peel-off imaging at every
 // scattering event (a separate instantiation); its FP64 body keeps the
 // registers it needs, at one wave.
-template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
+template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH, bool BEAM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_transport32(TransportArgs a) {
-  transport_body<float, ALIGNED, SPHERE, PEEL, TAB, MESH>(a);
+  transport_body<float, ALIGNED, SPHERE, PEEL, TAB, MESH, BEAM>(a);
 }
-template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH>
+template <bool ALIGNED, bool SPHERE, bool PEEL, bool TAB, bool MESH, bool BEAM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PEEL ? 1 : 2)))
 k_transport64(TransportArgs a) {
-  transport_body<double, ALIGNED, SPHERE, PEEL, TAB, MESH>(a);
+  transport_body<double, ALIGNED, SPHERE, PEEL, TAB, MESH, BEAM>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1867,12 +1864,25 @@ hipError_t launch_emission_table(const float* rho, const float* B, double fac, c
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// A pencil beam's runs have kernels with a drain of their own (wave_drain_runs; as a
+// branch of the others' it made the mesh's 4 % slower), except with peel-off, whose
+// events take the time, and tabulated grains, whose drains are per camera.
+static bool beam_kernel(int src_kind, bool peel, bool tab) { return src_kind == 1 && !peel && !tab; }
+
 template <bool A, bool S, bool T, bool M>
 static void launch_one(const TransportArgs& a, bool fp64, bool peel, int blocks, int bs, hipStream_t s) {
-  if (fp64 && peel) hipLaunchKernelGGL((k_transport64<A, S, true, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
-  else if (fp64) hipLaunchKernelGGL((k_transport64<A, S, false, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
-  else if (peel) hipLaunchKernelGGL((k_transport32<A, S, true, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
-  else hipLaunchKernelGGL((k_transport32<A, S, false, T, M>), dim3(blocks), dim3(bs), (size_t)a.tab_lds * 8, s, a);
+  const size_t lds = (size_t)a.tab_lds * 8;
+  if constexpr (!T) {
+    if (beam_kernel(a.src_kind, peel, T)) {
+      if (fp64) hipLaunchKernelGGL((k_transport64<A, S, false, T, M, true>), dim3(blocks), dim3(bs), lds, s, a);
+      else hipLaunchKernelGGL((k_transport32<A, S, false, T, M, true>), dim3(blocks), dim3(bs), lds, s, a);
+      return;
+    }
+  }
+  if (fp64 && peel) hipLaunchKernelGGL((k_transport64<A, S, true, T, M, false>), dim3(blocks), dim3(bs), lds, s, a);
+  else if (fp64) hipLaunchKernelGGL((k_transport64<A, S, false, T, M, false>), dim3(blocks), dim3(bs), lds, s, a);
+  else if (peel) hipLaunchKernelGGL((k_transport32<A, S, true, T, M, false>), dim3(blocks), dim3(bs), lds, s, a);
+  else hipLaunchKernelGGL((k_transport32<A, S, false, T, M, false>), dim3(blocks), dim3(bs), lds, s, a);
 }
 
 hipError_t launch_transport(const TransportArgs& a, bool fp64, bool aligned, bool sphere, bool peel, bool tab,
@@ -1898,34 +1908,37 @@ hipError_t launch_transport(const TransportArgs& a, bool fp64, bool aligned, boo
   return hipGetLastError();
 }
 
-template <bool A, bool S, bool PL, bool T, bool M>
+template <bool A, bool S, bool PL, bool T, bool M, bool B>
 static int occ_one(bool fp64, int bs, size_t lds) {
   int n = 0;
-  const hipError_t e = fp64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport64<A, S, PL, T, M>, bs, lds)
-                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport32<A, S, PL, T, M>, bs, lds);
+  const hipError_t e = fp64 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport64<A, S, PL, T, M, B>, bs, lds)
+                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_transport32<A, S, PL, T, M, B>, bs, lds);
   return e == hipSuccess ? n : 0;
 }
 
 template <bool A, bool S, bool T, bool M>
-static int occ_peel(bool fp64, bool peel, int bs, size_t lds = 0) {
-  return peel ? occ_one<A, S, true, T, M>(fp64, bs, lds) : occ_one<A, S, false, T, M>(fp64, bs, lds);
+static int occ_peel(bool fp64, bool peel, bool beam, int bs, size_t lds = 0) {
+  if constexpr (!T)
+    if (beam) return occ_one<A, S, false, T, M, true>(fp64, bs, lds);
+  return peel ? occ_one<A, S, true, T, M, false>(fp64, bs, lds) : occ_one<A, S, false, T, M, false>(fp64, bs, lds);
 }
 
 int transport_max_blocks_per_cu(bool fp64, bool aligned, bool sphere, bool peel, bool tab, bool mesh,
-                                int block_size, int tab_lds) {
+                                int src_kind, int block_size, int tab_lds) {
+  const bool beam = beam_kernel(src_kind, peel, tab);
   const size_t lds = (size_t)tab_lds * 8;
-  if (mesh && tab) return occ_peel<false, true, true, true>(fp64, peel, block_size, lds);
+  if (mesh && tab) return occ_peel<false, true, true, true>(fp64, peel, beam, block_size, lds);
   if (mesh) {
-    if (aligned && sphere) return occ_peel<true, true, false, true>(fp64, peel, block_size);
-    if (aligned) return occ_peel<true, false, false, true>(fp64, peel, block_size);
-    if (sphere) return occ_peel<false, true, false, true>(fp64, peel, block_size);
-    return occ_peel<false, false, false, true>(fp64, peel, block_size);
+    if (aligned && sphere) return occ_peel<true, true, false, true>(fp64, peel, beam, block_size);
+    if (aligned) return occ_peel<true, false, false, true>(fp64, peel, beam, block_size);
+    if (sphere) return occ_peel<false, true, false, true>(fp64, peel, beam, block_size);
+    return occ_peel<false, false, false, true>(fp64, peel, beam, block_size);
   }
-  if (tab) return occ_peel<false, true, true, false>(fp64, peel, block_size, lds);
-  if (aligned && sphere) return occ_peel<true, true, false, false>(fp64, peel, block_size);
-  if (aligned) return occ_peel<true, false, false, false>(fp64, peel, block_size);
-  if (sphere) return occ_peel<false, true, false, false>(fp64, peel, block_size);
-  return occ_peel<false, false, false, false>(fp64, peel, block_size);
+  if (tab) return occ_peel<false, true, true, false>(fp64, peel, beam, block_size, lds);
+  if (aligned && sphere) return occ_peel<true, true, false, false>(fp64, peel, beam, block_size);
+  if (aligned) return occ_peel<true, false, false, false>(fp64, peel, beam, block_size);
+  if (sphere) return occ_peel<false, true, false, false>(fp64, peel, beam, block_size);
+  return occ_peel<false, false, false, false>(fp64, peel, beam, block_size);
 }
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
