@@ -10,6 +10,7 @@
 #include <cmath>
 #include <utility>
 
+#include "kp_conv_rule.hpp"
 #include "kp_dn_device.hpp"
 #include "kp_dn_internal.hpp"
 
@@ -151,7 +152,6 @@ __device__ __forceinline__ void ct_for(F f) {
 }
 #define CT_INLINE __attribute__((always_inline))
 
-constexpr int CT_E = 18;              // halo columns (16 + 2)
 constexpr int CT_RSRC3 = 0x00020000;  // buffer resource word 3: raw 32-bit data
 constexpr int CT_OUT = 0x7FFFFFF0;    // an offset past every resource's range
 __device__ const u32x4 ct_zero[4] = {};
@@ -421,8 +421,6 @@ __global__ void __launch_bounds__(64 * WR * WC) k_conv3_tile(ConvArgs a) {
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-constexpr int CT_CUS = 256;
-
 template <int MODE, int NT, int RW, int WR, int WC, bool FAR = false>
 static void launch_tile(const ConvArgs& a, hipStream_t s) {
   using S = CtShape<NT, RW, WR, WC>;
@@ -431,31 +429,6 @@ static void launch_tile(const ConvArgs& a, hipStream_t s) {
   const long cap = (long)CT_CUS * (160 * 1024 / S::LDS);
   const long grid = std::min((items + 7) / 8 * 8, cap);
   hipLaunchKernelGGL((k_conv3_tile<MODE, NT, RW, WR, WC, FAR>), dim3((unsigned)grid), dim3(64 * S::NW), 0, s, a);
-}
-
-// The tile (rows 32, 16 or 8; nt x 16 channels) with the least estimated time
-// of its busiest CU: a step of 32 input channels costs 0.45 us whatever its
-// size (its loads' latency, shared by the workgroups resident on a CU) and
-// rows (0.004 + 0.0165 nt) us of MFMAs.  Fitted to 25 x 43 x 2 images, 192 ->
-// 192 (us by rows 32 / 16 / 8: nt 4 18.1 / 12.3 / 8.7, nt 2 11.8 / 8.1 / 6.5,
-// nt 1 8.9 / 6.9 / 6.9); 256^2 x 8, 144 -> 48, nt 3 67 / 73 / 85; 100 x 172 x 2,
-// 144 -> 48, nt 3 14.6 / 12.0 / 11.5, nt 1 15.3 / 10.6 / 12.0.
-void conv_tile_shape(const ConvArgs& a, int& rows, int& nt) {
-  double best = 1e30;
-  const int t16 = a.nout / 16, nb = (a.cin + 31) / 32;
-  for (int r : {32, 16, 8})
-    for (int n : {4, 3, 2, 1}) {
-      if (t16 % n) continue;
-      const double items = (double)a.B * ((a.H + r - 1) / r) * ((a.W + 15) / 16) * (t16 / n);
-      const int lds = 2 * 1024 * (((r + 2) * CT_E + 15) / 16 + 9 * n) + 2048, res = 160 * 1024 / lds;
-      const double t = nb * (0.45 * std::ceil(items / (CT_CUS * res)) +
-                             std::ceil(items / CT_CUS) * r * (0.004 + 0.0165 * n));
-      if (t < best) {
-        best = t;
-        rows = r;
-        nt = n;
-      }
-    }
 }
 
 template <int MODE>
@@ -467,7 +440,7 @@ static void conv3_mode(const ConvArgs& a, hipStream_t s) {
     return;
   }
   int rows, nt;
-  conv_tile_shape(a, rows, nt);
+  conv_tile_shape(a.B, a.H, a.W, a.cin, a.nout, rows, nt);
   // bytes from a tile's first row to its last
   const bool far = (double)(rows + 2) * a.W * std::max(a.xs, a.xl ? a.xls : 0) * 2.0 >= 2147000000.0;
   switch (far ? -nt : rows * 8 + nt) {
