@@ -3,6 +3,7 @@
 // timing with HIP events recorded on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -603,18 +604,11 @@ kp_status transport_launch(kp_ctx* ctx, const kp_opts* o, uint64_t total, const 
   // non-spherical) grains, FP32 otherwise
   const bool fp64 = o->transport_fp64 == 1 || (o->transport_fp64 == 0 && aligned && !sphere);
   const int bs = o->block_size ? o->block_size : 256;
-  int bpc = o->blocks_per_cu;
-  if (bpc == 0) {
-    bpc = transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh, a.src_kind, bs,
-                                      a.tab_lds);
-    if (bpc < 1) bpc = 1;
-    if (bpc > 8) bpc = 8;
-  }
+  const int fit = std::max(1, transport_max_blocks_per_cu(fp64, aligned, sphere, b.peel != nullptr, tab, ctx->have_mesh,
+                                                          a.src_kind, bs, a.tab_lds));
+  const int bpc = o->blocks_per_cu ? o->blocks_per_cu : std::min(fit, 8);
   uint64_t blocks = (uint64_t)ctx->cu_count * bpc;
-  // packets per wavefront: all lanes, or, of a run that does not fill the chip, an
-  // equal share
-  const uint64_t waves = blocks * (uint64_t)(bs / 64), share = (total + waves - 1) / waves;
-  a.lanes = share < 64 ? (int)share : 64;
+  a.lanes = packets_per_wave(total, (uint64_t)ctx->cu_count * std::min(bpc, fit), bs / 64);
   const uint64_t per_block = (uint64_t)a.lanes * (uint64_t)(bs / 64);
   const uint64_t need_blocks = (total + per_block - 1) / per_block;
   if (blocks > need_blocks) blocks = need_blocks;

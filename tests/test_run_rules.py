@@ -33,11 +33,13 @@ int events(int batch, int lanes, int nactive, int exhausted, int peel) {
 void pixels(unsigned npx, unsigned npy, int* xy) {
   for (unsigned p = 0; p < npx * npy; ++p) image_pixel(p, npx, npy, xy[2 * p], xy[2 * p + 1]);
 }
+int lanes(size_t total, size_t blocks, int waves) { return packets_per_wave(total, blocks, waves); }
 size_t waves(size_t npix, size_t maps) { return (size_t)image_waves(npix, maps); }
 size_t grow(size_t need, size_t have, size_t elem) { return grow_bytes(need, have, elem); }
 }
 """)
     dll.copies.argtypes = [C.c_int, z, z, z, z, z]
+    dll.lanes.argtypes = [z, z, C.c_int]
     dll.waves.argtypes, dll.waves.restype = [z, z], z
     dll.grow.argtypes, dll.grow.restype = [z, z, z], z
     return dll
@@ -130,3 +132,13 @@ def test_image_wavefronts_have_pixels(lib):
             waves = lib.waves(npix, maps)
             assert 64 * waves >= npix * maps
             assert 0.7 * 64 * (waves - 1) <= npix * maps, (npix, maps)
+
+
+def test_packets_per_wavefront(lib):
+    """A share that covers the run with the blocks that run at a time, and no more
+    than a packet per wavefront above it."""
+    for total in (1, 2, 63, 3072, 3073, 20000, 196607, 196608, 300000, 10 ** 9):
+        for blocks, waves in ((256, 4), (768, 4), (768, 1), (2048, 2)):
+            n = lib.lanes(total, blocks, waves)
+            assert 1 <= n <= 64
+            assert n == 64 or (n - 1) * blocks * waves < total <= n * blocks * waves
