@@ -53,7 +53,7 @@ def counter_record():
     rec = json.load(open(path))
     csrc = os.path.join(ROOT, "paper_2512_01283_amd", "csrc")
     src = b"".join(open(os.path.join(csrc, f), "rb").read()
-                   for f in ("kp_kernels.hip", "kp_device.hpp", "kp_internal.hpp", "kp_transfer.hpp"))
+                   for f in ("kp_kernels.hip", "kp_device.hpp", "kp_internal.hpp", "kp_transfer.hpp", "kp_rules.hpp"))
     if hashlib.sha256(src).hexdigest() != rec["source_sha256"]:
         return None
     return rec
@@ -73,8 +73,10 @@ def atomic_calibration(lines: int = ATOMIC_CAL_LINES, reps: int = 3, order: int 
     """64-byte-line FP64 atomics the device sustains, in lines/s: the tally
     flush's own access pattern (lane L adds component L % 6 of block L / 6,
     one wave covering 10 blocks) over the blocks of a [256^3][8] FP64 array
-    in uniformly random (order 0) or consecutive (order 1) order, in
-    libkpcalib.so (csrc/kp_calib.hip); best of `reps` launches, HIP events."""
+    in uniformly random (order 0) or consecutive (order 1) order, or random
+    over its first 64 MB with indices that are formed, not read (order 2: what
+    the L2 takes), in libkpcalib.so (csrc/kp_calib.hip); best of `reps`
+    launches, HIP events."""
     import ctypes as C
     path = os.path.join(ROOT, "paper_2512_01283_amd", "libkpcalib.so")
     if not os.path.exists(path):
@@ -188,6 +190,7 @@ def main():
         return
     if args.atomic_calibration:
         print(json.dumps({"atomic_calibration_lines": ATOMIC_CAL_LINES,
+                          "l2_lines_per_s": atomic_calibration(order=2),
                           "consecutive_lines_per_s": atomic_calibration(order=1),
                           "uniform_random_lines_per_s": atomic_calibration(order=0)}))
         return
@@ -323,23 +326,26 @@ def main():
             d["train_wgrad_mfma_frac"] = d["train_wgrad_tflops"] / BF16_PEAK_TFLOPS
         out["detail"]["denoiser"] = d
         dn.close()
-    # the transport's binding resource: tally-line atomics, against what a
-    # plain scatter-add of the same shape sustains on this device with the
-    # most locality (consecutive lines: the bound) and with none (uniformly
-    # random lines)
+    # the transport's binding resource: tally-line atomics, against what the
+    # L2 takes from a kernel that does nothing else (the bound), and what a
+    # plain scatter-add of the same shape sustains over the whole array with
+    # consecutive and with uniformly random lines
+    cal_l2 = atomic_calibration(order=2)
     cal_seq = atomic_calibration(order=1)
     cal = atomic_calibration(order=0)
     lines = float(np.mean(flushes))
     achieved = lines / (avg_t * 1e-3)
     out["detail"]["atomic_roofline"] = {
         "bound": "64-byte-line FP64 atomics (tally flush)",
-        "achieved_lines_per_s": achieved, "calibrated_lines_per_s": cal_seq,
-        "frac": achieved / cal_seq, "lines_per_launch": lines,
+        "achieved_lines_per_s": achieved, "calibrated_lines_per_s": cal_l2,
+        "frac": achieved / cal_l2, "lines_per_launch": lines,
+        "consecutive_lines_per_s": cal_seq, "frac_of_consecutive": achieved / cal_seq,
         "uniform_random_lines_per_s": cal, "frac_of_uniform_random": achieved / cal,
         "lines_unit": "tally cell blocks flushed per transport launch (kp_stats.tally_flushes), "
                       "one 64-byte block of six FP64 each",
         "calibration": "2^24 64-byte blocks of a [256^3][8] FP64 array, six FP64 atomics each in the "
-                       "flush's lane pattern, consecutive (the bound) and uniformly random, best of 3 each "
+                       "flush's lane pattern: random over 64 MB with indices formed (the bound), consecutive "
+                       "and uniformly random over the whole array with indices read, best of 3 each "
                        "(bench.py --atomic-calibration, csrc/kp_calib.hip)"}
     if not args.no_cpu_baseline:
         print("timing the oracle on a bounded sample ...", file=sys.stderr, flush=True)

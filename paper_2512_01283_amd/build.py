@@ -37,9 +37,9 @@ FLAGS = [
 SOURCE_FLAGS = {
     "kp_kernels.hip": ["-mllvm", "-disable-machine-licm", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
     "kp_image.hip": ["-mllvm", "-disable-machine-licm"],
-    # accumulators in ordinary registers: in the others they are copied back and forth around every epilogue
     # the operands' addresses in the second LDS buffer are not worth registers kept over the loop
     "kp_wgrad.hip": ["-mllvm", "-disable-machine-licm"],
+    # accumulators in ordinary registers: in the others they are copied back and forth around every epilogue
     "kp_conv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 

@@ -141,17 +141,6 @@ __global__ void __launch_bounds__(256) k_conv3(ConvArgs a) {
 // 27 us are its 134 MB of maps at the rate of a copy.  Two images of 100 x 172,
 // 48 -> 48: 14.3 -> 6.6 us; of 25 x 43, 192 -> 192: 26.5 -> 6.7 us.
 // ---------------------------------------------------------------------------
-// compile-time loop: the body sees its index as a constant
-template <class F, int... I>
-__device__ __forceinline__ void ct_seq(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void ct_for(F f) {
-  ct_seq(f, std::make_integer_sequence<int, N>{});
-}
-#define CT_INLINE __attribute__((always_inline))
-
 constexpr int CT_RSRC3 = 0x00020000;  // buffer resource word 3: raw 32-bit data
 constexpr int CT_OUT = 0x7FFFFFF0;    // an offset past every resource's range
 __device__ const u32x4 ct_zero[4] = {};
@@ -203,7 +192,7 @@ __device__ __forceinline__ void conv3_tile(const ConvArgs& a) {
   // 16-byte slot of chunk c of halo column hx / operand row r
   auto swz = [&](int hx, int c) CT_INLINE { return c ^ (((hx >> 2) & 1) << 1); };
   // offsets of this lane's halo chunks from the tile's corner in the current
-  // source, CT_OUT outside the image: bytes, or pixels where a.far is set
+  // source, CT_OUT outside the image: bytes, or (FAR) pixels
   int hoff[S::HU];
   const uint16_t* xbase = nullptr;
   int xstride = 0;

@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 namespace kp {
 namespace dn {
 
@@ -59,6 +61,17 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
                                                  0, 0, 0);
 }
+
+// compile-time loop: the body sees its index as a constant
+template <class F, int... I>
+__device__ __forceinline__ void ct_seq(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void ct_for(F f) {
+  ct_seq(f, std::make_integer_sequence<int, N>{});
+}
+#define CT_INLINE __attribute__((always_inline))
 
 }  // namespace dn
 }  // namespace kp

@@ -370,7 +370,10 @@ static void launch_image_one(const ImageArgs& a, bool aligned, bool sphere, dim3
   // their rays then cross 4 MB of the tally per step on each XCD, all of its L2, and a
   // line is gone before the neighbouring rays reach it.  Half a CU's LDS, not
   // used, keeps it at two blocks: 256^3 disk 2.62 (four), 2.28 (three), 1.94 ms
-  // (two), 2.40 (one); grids that fit the L2s measured the same either way.
+  // (two), 2.40 (one).  The limit is for the largest grids, whose time it is about:
+  // uniform spheres, 8 views of 256^2, with it and without, 256^3 1.97 and 2.44 ms,
+  // 192^3 1.03 and 1.11, 160^3 0.76 and 0.73, 128^3 0.57 and 0.52, 64^3 0.29 and 0.23,
+  // and with 8 wavelengths 128^3 4.5 and 3.3.
   const size_t lds = sphere && !U && !M && !X && bs == 256 ? size_t(80) << 10 : 0;
   if (sphere) hipLaunchKernelGGL((k_image<false, true, U, M, X>), grid, dim3(bs), lds, s, a);
   else if (aligned) hipLaunchKernelGGL((k_image<true, false, U, M, X>), grid, dim3(bs), 0, s, a);

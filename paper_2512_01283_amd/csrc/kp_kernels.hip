@@ -5,25 +5,24 @@
 // Step 1 is a persistent packet-per-lane loop: every lane of a 64-wide
 // wavefront carries one photon packet and advances it by one cell segment per
 // iteration (plus the scattering event that may end the segment); lanes whose
-// packet ended are refilled from a global work counter once per iteration
-// (one atomic per wavefront, ids handed out by lane rank), so long and short
-// paths do not idle a wavefront.  Packets are independent: each draws from its
-// own Philox stream (key (seed, wavelength), counter (packet, block, 0, 0)),
-// so the schedule never changes a packet's path.
+// packet ended are refilled from a global work counter for several of them at a
+// time (ids handed out by lane rank), so long and short paths do not idle a
+// wavefront.  Packets are independent: each draws from its own Philox stream
+// (key (seed, wavelength), counter (packet, block, 0, 0)), so the schedule never
+// changes a packet's path.
 //
 // The scattering-source tally of step 1 is kept as the incident coherency of
 // each cell (3x3 Hermitian, 9 reals): because every scatterer here is a
 // dipole, the source toward any camera is a fixed linear map of it (formed in
 // step 2), so one tally serves all views and wavelengths' views at 9 FP64
 // atomics per segment instead of 4 per view (6 when no circular polarisation
-// can arise, i.e. for spheres).  A lane keeps the running sum for its current
-// cell in registers and hands it over only when it moves to another cell
-// (multiple scattering inside a thick cell costs no atomics).  Hand-overs are
-// flushed cooperatively by the whole wavefront: the pending sums are staged in
-// LDS and re-issued so that one atomic instruction carries the contiguous
-// components of ~7-10 cells, each cell's block aligned to one cache line
-// (64 B for 6 reals, 128 B for 9) -- memory-side FP64 atomics are charged per
-// line request, so this is ~5x cheaper than one cell per lane.
+// can arise, i.e. for spheres).  Segments are staged in LDS, those of one lane in
+// the same cell added up there while its entry is staged (multiple scattering
+// inside a thick cell then costs few atomics), and flushed cooperatively by the
+// whole wavefront: one atomic instruction carries the contiguous components of
+// ~7-10 cells, each cell's block aligned to one cache line (64 B for 6 reals,
+// 128 B for 9) -- memory-side FP64 atomics are charged per line request, so this
+// is ~5x cheaper than one cell per lane.
 #include "kp_transfer.hpp"
 
 namespace kp {
@@ -407,7 +406,9 @@ __device__ __forceinline__ Quat<R> quat_cast(const Quat<double>& q) {
 // Tally flush, wave-cooperative and deferred.  A lane's tallied segment is
 // staged as (key, NC values) in its wavefront's LDS area (wave_stage), or,
 // when it lies in the cell of the lane's last entry and that is still there,
-// added to it (multiple scattering inside a thick cell costs no atomics);
+// added to it (a drain forgets the entries: a lane that stays in a cell across one
+// adds a second line, 1 % more lines on the disk and up to 2.3 times as many in a
+// scattering sphere of depth 100, for the 12-18 registers a sum of its own takes);
 // when the area may not hold another full wavefront of entries, wave_drain
 // adds all staged entries to the tally: lane L adds component L % NC of entry
 // L / NC, so one atomic instruction covers 64 / NC whole cells.  Deferring
@@ -1477,9 +1478,11 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
   constexpr bool CHUNKED = SPHERE;
   constexpr unsigned long long WAVE_CHUNK = 64;
   // Lanes refilled together: a start costs ~900 instructions (Philox, sines, a
-  // logarithm, divisions) whatever the number of lanes that run it.  1, 8 and 16
-  // lanes: aligned slab 39.6, 33.6, 27.3 ms; aligned disk 15.0, 13.7, 13.8;
-  // spherical disk within 1 %.
+  // logarithm, divisions) whatever the number of lanes that run it, and lanes that
+  // wait for one are idle.  One lane at a time: aligned disk +9 %.  8 and 16 lanes,
+  // whole calls: aligned slab 16.51, 16.73 ms; aligned disk 15.59, 15.78; 8
+  // wavelengths 35.51, 35.70; mesh 41.08, 41.35; spherical disk 9.27, 9.28, at 1e8
+  // packets 609.9, 607.4.
   constexpr int REFILL_BATCH = 8;
   // a refill hands up to 64 idle lanes ids from one new chunk
   static_assert(WAVE_CHUNK >= 64, "a chunk must cover a whole wavefront");
@@ -1614,8 +1617,8 @@ __device__ __forceinline__ void transport_body(const TransportArgs& a) {
 // written for: with the rarely touched state in LDS (Cold), the arguments of
 // the rare paths read again where they are used (reload_args) and machine
 // LICM off (it would hold the literals of every path in registers across the
-// loop), the sphere kernel takes 125 registers (253 before), tables 185, the mesh
-// 161 and the FP64 kernel of aligned grains 200 (361), none with a spill:
+// loop), the sphere kernel takes 127 registers (253 before), tables 193, the mesh
+// 161 and the FP64 kernel of aligned grains 201 (361), none with a spill:
 // three waves per SIMD for spheres and the mesh and two for aligned grains in FP64
 // (which spilled 50-190 registers at two before).  256^3 disk, 1e6 packets:
 // 8.44 -> 7.17 ms, 3e7: 213.5 -> 173.0 ms; aligned grains, 1e6: 21.9 -> 13.4 ms;

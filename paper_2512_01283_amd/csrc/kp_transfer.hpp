@@ -1,7 +1,7 @@
 // kp_transfer.hpp -- device code shared by the transport (kp_kernels.hip) and
 // the imaging (kp_image.hip) kernels: complex arithmetic, extinction
-// coefficients, the composite mesh, the tally's per-cell block and the
-// Appendix A cell solution.
+// coefficients, the composite mesh and the tally's per-cell block; and the
+// Appendix A cell solution of peel-off.
 #pragma once
 #include "kp_device.hpp"
 #include "kp_internal.hpp"
@@ -129,7 +129,8 @@ template <bool SPHERE> struct TallyShape {
 };
 
 // ---------------------------------------------------------------------------
-// Step 2 and peel-off: the Appendix A solution in its eigenbasis.
+// Peel-off: the Appendix A solution in its eigenbasis (step 2 has its own form of
+// it, dichroic_cell in kp_image.hip).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void appA_eigen(double a1, double a2, double a3, double dtau,
                                            const double src[4], double s[4]) {

@@ -49,16 +49,6 @@ namespace dn {
 // consecutive pixels and the 4 that lie 8 further on, and their 8 segments
 // fall on different banks at every horizontal shift.
 // ---------------------------------------------------------------------------
-template <class F, int... I>
-__device__ __forceinline__ void wt_seq(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void wt_for(F f) {
-  wt_seq(f, std::make_integer_sequence<int, N>{});
-}
-#define WT_INLINE __attribute__((always_inline))
-
 constexpr int WT_ROWS = 8, WT_COLS = 32;             // pixels of a tile
 constexpr int WT_E = WT_COLS + 2;                    // halo columns
 constexpr int WT_XP = (WT_ROWS + 2) * WT_E;          // halo pixels (340)
@@ -99,9 +89,9 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
 
   // loads: piece n holds pixels 8n..8n+7, this lane 16-byte slot lane & 7 of pixel 8n + (lane >> 3)
   const int slot = lane & 7, lpx = lane >> 3;
-  auto chunk_of = [&](int p) WT_INLINE { return slot ^ (2 * wt_swz(p)); };  // channels 8 chunk..
+  auto chunk_of = [&](int p) CT_INLINE { return slot ^ (2 * wt_swz(p)); };  // channels 8 chunk..
   int xrel[WT_XU], xpos[WT_XU];  // offset from the tile's corner; row << 8 | column
-  wt_for<WT_XU>([&](auto U) WT_INLINE {
+  ct_for<WT_XU>([&](auto U) CT_INLINE {
     const int px = 8 * (wv + 8 * U) + lpx, hy = px / WT_E, hx = px - hy * WT_E, ch = chunk_of(hx);
     const int pix = low ? ((hy + 1) >> 1) * Ws + ((hx + 1) >> 1) : hy * Ws + hx;
     const bool ok = px < WT_XP && ch < 2 * G && c0 + 8 * ch < a.cin;
@@ -115,7 +105,7 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
   const uint16_t *xb = nullptr, *zb = nullptr;
   __amdgpu_buffer_rsrc_t xr, zr;
   int y0 = 0, x0 = 0;
-  auto prep = [&](int t) WT_INLINE {
+  auto prep = [&](int t) CT_INLINE {
     const int img = t / (tyn * txn), rt = t - img * tyn * txn;
     y0 = (rt / txn) * WT_ROWS;
     x0 = t < t_end ? (rt % txn) * WT_COLS : a.W + 1;
@@ -124,7 +114,7 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
     xr = __builtin_amdgcn_make_buffer_rsrc((void*)xb, 0, WT_OUT - 16, WT_RSRC3);
     zr = __builtin_amdgcn_make_buffer_rsrc((void*)zb, 0, WT_OUT - 16, WT_RSRC3);
   };
-  auto piece = [&](auto K, unsigned char* buf) WT_INLINE {
+  auto piece = [&](auto K, unsigned char* buf) CT_INLINE {
     constexpr int k = K;
     constexpr bool is_x = k < WT_XU;
     constexpr int u = is_x ? k : k - WT_XU;
@@ -150,48 +140,48 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
   // operands: this lane points at channels 4 (lane & 3).. of pixel 8g + (lane >> 2 & 3) (and 4 further on)
   const int lc = 8 * (lane & 3), lp = 8 * g + ((lane >> 2) & 3);
   int xo[3][2], zo[2];
-  wt_for<3>([&](auto D) WT_INLINE {
-    wt_for<2>([&](auto H) WT_INLINE {
+  ct_for<3>([&](auto D) CT_INLINE {
+    ct_for<2>([&](auto H) CT_INLINE {
       const int p = lp + D + 4 * H;
       xo[D][H] = (set * RS * WT_E + p) * 128 + 32 * (cg ^ wt_swz(p)) + lc;
     });
   });
-  wt_for<2>([&](auto H) WT_INLINE {  // segment M lies at ^ 32 M
+  ct_for<2>([&](auto H) CT_INLINE {  // segment M lies at ^ 32 M
     const int p = lp + 4 * H;
     zo[H] = WT_XI * 1024 + (set * RS * WT_COLS + p) * 128 + 32 * wt_swz(p) + lc;
   });
   f32x4 acc[MR][9];
-  wt_for<MR>([&](auto M) WT_INLINE { wt_for<9>([&](auto T) WT_INLINE { acc[M][T] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
+  ct_for<MR>([&](auto M) CT_INLINE { ct_for<9>([&](auto T) CT_INLINE { acc[M][T] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
   float bsum[MR];
-  wt_for<MR>([&](auto M) WT_INLINE { bsum[M] = 0.f; });
+  ct_for<MR>([&](auto M) CT_INLINE { bsum[M] = 0.f; });
   const bool do_bias = first && cg == 0;
 
-  auto rows = [&](const unsigned char* cur, unsigned char* nxt) WT_INLINE {
+  auto rows = [&](const unsigned char* cur, unsigned char* nxt) CT_INLINE {
     u32x4 A[3][MR];  // gz rows r, r - 1, r - 2
-    wt_for<RS + 2>([&](auto R) WT_INLINE {
+    ct_for<RS + 2>([&](auto R) CT_INLINE {
       constexpr int r = R;
       u32x4 x[3];
-      wt_for<3>([&](auto D) WT_INLINE {
+      ct_for<3>([&](auto D) CT_INLINE {
         x[D] = wt_read(cur + xo[D][0] + r * WT_E * 128, cur + xo[D][1] + r * WT_E * 128);
       });
       if constexpr (r < RS)
-        wt_for<MR>([&](auto M) WT_INLINE {
+        ct_for<MR>([&](auto M) CT_INLINE {
           A[r % 3][M] = wt_read(cur + (zo[0] ^ (32 * M)) + r * WT_COLS * 128, cur + (zo[1] ^ (32 * M)) + r * WT_COLS * 128);
         });
-      wt_for<PG>([&](auto J) WT_INLINE {
+      ct_for<PG>([&](auto J) CT_INLINE {
         if constexpr (r * PG + J < NP) piece(std::integral_constant<int, r * PG + J>{}, nxt);
       });
       // the oldest gz row first: its products need nothing that was just read of gz
-      wt_for<3>([&](auto Q) WT_INLINE {
+      ct_for<3>([&](auto Q) CT_INLINE {
         constexpr int dy = 2 - Q, y = r - dy;
         if constexpr (y >= 0 && y < RS)
-          wt_for<3>([&](auto D) WT_INLINE {
-            wt_for<MR>([&](auto M) WT_INLINE { acc[M][3 * dy + D] = mfma(A[y % 3][M], x[D], acc[M][3 * dy + D]); });
+          ct_for<3>([&](auto D) CT_INLINE {
+            ct_for<MR>([&](auto M) CT_INLINE { acc[M][3 * dy + D] = mfma(A[y % 3][M], x[D], acc[M][3 * dy + D]); });
           });
       });
       if constexpr (r < RS)
         if (do_bias)
-          wt_for<MR>([&](auto M) WT_INLINE {
+          ct_for<MR>([&](auto M) CT_INLINE {
             float f[8];
             unpack8(A[r % 3][M], f);
             bsum[M] += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
@@ -201,8 +191,8 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
   };
   int t = t_begin;
   prep(t);
-  wt_for<NP>([&](auto K) WT_INLINE { piece(K, lds0); });
-  auto step = [&](unsigned char* cur, unsigned char* nxt) WT_INLINE {
+  ct_for<NP>([&](auto K) CT_INLINE { piece(K, lds0); });
+  auto step = [&](unsigned char* cur, unsigned char* nxt) CT_INLINE {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // this wave's loads into cur have landed (vmcnt 0)
     __syncthreads();
     prep(++t);  // past the last tile the loads go on and find nothing
@@ -217,23 +207,23 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
   __syncthreads();
   // the row sets' sums meet in LDS, one set after the other: 16 output
   // channels [co][tap][c] of the block after the other, then the biases
-  wt_for<MR>([&](auto M) WT_INLINE {
+  ct_for<MR>([&](auto M) CT_INLINE {
     bsum[M] += __shfl_xor(bsum[M], 16);
     bsum[M] += __shfl_xor(bsum[M], 32);
   });
   // (rows of 144 G + 4 floats: the four co of a store fall on different banks)
   constexpr int NB = 16 * 9 * 16 * G, ROW = 9 * 16 * G + 4;
   static_assert(2 * 16 * ROW * 4 <= WT_BUF && 16 * ROW * 4 + 16 * MR * 4 <= WT_BUF && MR <= 3);
-  auto slab = [&](int m) WT_INLINE { return (float*)(m < 2 ? lds0 : lds1) + (m < 2 ? m : 0) * 16 * ROW; };
+  auto slab = [&](int m) CT_INLINE { return (float*)(m < 2 ? lds0 : lds1) + (m < 2 ? m : 0) * 16 * ROW; };
   float* const bias = (float*)lds1 + 16 * ROW;
-  auto merge = [&](auto ADD) WT_INLINE {
-    wt_for<MR>([&](auto M) WT_INLINE {
-      wt_for<4>([&](auto J) WT_INLINE {
+  auto merge = [&](auto ADD) CT_INLINE {
+    ct_for<MR>([&](auto M) CT_INLINE {
+      ct_for<4>([&](auto J) CT_INLINE {
         float* q = slab(M) + (4 * g + J) * ROW + 16 * cg + i;
         float v[9];
-        wt_for<9>([&](auto T) WT_INLINE { v[T] = acc[M][T][(int)J]; });
-        if constexpr (ADD) wt_for<9>([&](auto T) WT_INLINE { v[T] += q[T * 16 * G]; });
-        wt_for<9>([&](auto T) WT_INLINE { q[T * 16 * G] = v[T]; });
+        ct_for<9>([&](auto T) CT_INLINE { v[T] = acc[M][T][(int)J]; });
+        if constexpr (ADD) ct_for<9>([&](auto T) CT_INLINE { v[T] += q[T * 16 * G]; });
+        ct_for<9>([&](auto T) CT_INLINE { q[T * 16 * G] = v[T]; });
         __builtin_amdgcn_sched_barrier(0);  // nine at a time (registers)
       });
       if (do_bias && g == 0) bias[16 * M + i] = ADD ? bias[16 * M + i] + bsum[M] : bsum[M];
@@ -245,7 +235,7 @@ __device__ __forceinline__ void wgrad_block(const WgradLayer& a, int m0, int c0,
     if (set == s) merge(std::true_type{});
     __syncthreads();
   }
-  wt_for<MR>([&](auto M) WT_INLINE {
+  ct_for<MR>([&](auto M) CT_INLINE {
     for (int k = 4 * threadIdx.x; k < NB; k += 4 * 512) {
       const int co = k / (9 * 16 * G);
       *(f32x4*)(part + M * NB + k) = *(const f32x4*)(slab(M) + k + 4 * co);
@@ -349,7 +339,9 @@ static void wgrad_units(int cin, int units[3]) {
   units[2] = c16 % 4 == 1;
 }
 // us of a workgroup's tile and outside its tiles, measured on eight 256^2 maps: mr 3
-// 1.95 / 2.2 / 3.4 us for 16 / 32 / 64 input channels, mr 2 1.55 us for 16, 2.2 for 64
+// 1.95 / 2.2 / 3.4 us for 16 / 32 / 64 input channels, mr 2 1.55 us for 16, 2.2 for 64;
+// mr 1 1.7 for 16 (widths 16) and 2.3 for 64 (widths 112): more than is taken here, in
+// nearly the ratio that is, and only the ratio shares out the chunks
 static double wgrad_tile_us(int mr, int G) { return 1.35 + G * (mr == 3 ? 0.5 : mr == 2 ? 0.22 : 0.1); }
 constexpr double WT_FIXED_US = 8.0;
 
